@@ -36,9 +36,10 @@
  *
  * Allocation.  The matrix products run on rocBLAS.  Their scratch is a
  * 32 MiB slice of the caller's workspace, handed to rocBLAS
- * (rocblas_set_workspace) after a size query has confirmed the products fit
- * in it (else KARA_ERR_WORKSPACE), so rocBLAS allocates no workspace of its
- * own.  The one thing the library creates on this path is the rocBLAS
+ * (rocblas_set_workspace), so rocBLAS allocates no workspace of its own.  A
+ * product that does not fit it ends the call with KARA_ERR_WORKSPACE; the
+ * steps before it may be enqueued by then, so hidden_out and q_out are
+ * unspecified.  The one thing the library creates on this path is the rocBLAS
  * handle: kara_recompute_queries makes one per device on its first call
  * there (rocblas_create_handle: rocBLAS's host state and whatever device
  * memory the handle takes for itself) and keeps it until the process ends;

@@ -230,6 +230,14 @@ def test_recompute_pass_layers(window, n_q, n_kv, d, D, F, bs):
     for l in range(L):
         assert torch.equal(q_all[l].view(torch.int16), q_layers[l].view(torch.int16)), f"layer {l} queries"
     assert torch.equal(h_all, h)
+    # in place (hidden_out is hidden_in), with scratch full of ones so that a
+    # product run ahead of its inputs would show: the same bits
+    h_inout = h0.clone()
+    wsp.view(torch.bfloat16)[:wsp.numel() // 2].fill_(1.0)
+    kara.recompute_queries(params, model, trig, wts, h_inout, h_inout, kp, vp, bt, lens, ws, rope_pos0, q_all, status,
+                           wsp)
+    torch.cuda.synchronize()
+    assert torch.equal(h_inout, h) and torch.equal(q_all[L - 1].view(torch.int16), q_layers[L - 1].view(torch.int16))
     # after the first call on the device, calls allocate nothing: the device's
     # free memory is unchanged across another full call
     torch.cuda.synchronize()
