@@ -43,6 +43,7 @@ constexpr int kKeys = 64;                   // keys per chunk
 constexpr int kStages = 4;                  // LDS ring: chunks ch .. ch+3 resident or in flight
 constexpr int kLookahead = kStages - 1;     // chunks copied ahead of the one being worked on
 constexpr int kPageTbl = 2048;              // block-table entries held in LDS at a time
+constexpr int kCUs = 256;
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kNegInf = -__builtin_huge_valf();
 constexpr float kMaxFloor = -1e30f;         // finite start of a running maximum
@@ -91,6 +92,8 @@ struct AttnArgs {
   const int32_t* status;
   char* out;                  // [n_trig][W][Hq][d]
   int n_rb;                   // row blocks per (sequence, KV head)
+  int parts;                  // pieces a unit's row blocks are dealt in (see launch_attn_t)
+  int rb_part;                // row blocks per piece, rounded up
   int64_t n_blocks;
 };
 
@@ -163,13 +166,41 @@ __global__ __launch_bounds__(kAttnThreads, 1) void attn_kernel(AttnArgs a) {
   const int gq = lane >> 4;
   const int li = lane & 15;
 
-  // blocks of one (sequence, KV head) together on one XCD, heaviest first
-  int64_t bid = blockIdx.x;
-  if ((a.n_blocks & 7) == 0) bid = (bid & 7) * (a.n_blocks >> 3) + (bid >> 3);
-  const int64_t unit = bid / a.n_rb;
-  const int rb = a.n_rb - 1 - (int)(bid % a.n_rb);
+  // Blocks go round-robin to the 8 XCDs.  Unit (sequence, KV head) u's
+  // pieces u*parts .. go to XCDs (u*parts + part) % 8, all row blocks of a
+  // piece to one XCD, so they share its L2 copy of the keys, and (eight KV
+  // heads) every XCD gets a head of every sequence.  Sequences are taken in
+  // descending context length, so the longest blocks start first and the
+  // short ones fill the end.  16 sequences of 4K-16K tokens, 32/8 heads:
+  // 3.18 ms a layer with a run of whole sequences per XCD (the XCD with the
+  // longest pair finished last), 2.43 ms dealt this way (1075 TFLOP/s).
+  const int64_t slot_x = blockIdx.x >> 3;
+  const int64_t piece = slot_x / a.rb_part * 8 + (blockIdx.x & 7);
+  const int64_t unit = piece / a.parts;
+  const int rb = a.n_rb - 1 - ((int)(piece % a.parts) * a.rb_part + (int)(slot_x % a.rb_part));
   const int h = (int)(unit % a.Hkv);
-  const int t = (int)(unit / a.Hkv);
+  int t = (int)(unit / a.Hkv);
+  if (rb < 0) return;         // the last piece of a unit may be short
+  if (a.n_trig > 1 && a.n_trig <= kAttnThreads) {
+    // t: the sequence of rank t by context length (flagged ones last)
+    int len = -1;
+    if (tid < a.n_trig) {
+      len = a.status[tid] == 0 ? a.win_start[a.trig[tid]] : -1;
+      ptbl[tid] = (uint32_t)len;
+    }
+    __syncthreads();
+    if (tid < a.n_trig) {
+      int rank = 0;
+      for (int o = 0; o < a.n_trig; ++o) {
+        const int lo = (int)ptbl[o];
+        rank += lo > len || (lo == len && o < tid);
+      }
+      if (rank == t) ptbl[kPageTbl - 1] = (uint32_t)tid;
+    }
+    __syncthreads();
+    t = (int)__builtin_amdgcn_readfirstlane(ptbl[kPageTbl - 1]);
+    __syncthreads();
+  }
   if (a.status[t] != 0) return;
   const int s = a.trig[t];
   const int p0 = a.win_start[s];
@@ -464,10 +495,28 @@ template <int D, int QT>
 hipError_t launch_attn_t(AttnArgs a, hipStream_t stream) {
   using C = ACfg<D, QT>;
   a.n_rb = (a.G * a.W + C::kRowsWG - 1) / C::kRowsWG;
-  a.n_blocks = (int64_t)a.n_trig * a.Hkv * a.n_rb;
-  if (a.n_blocks == 0) return hipSuccess;
+  // units in the fewest pieces (1, 2, 4 or 8) that make their count a
+  // multiple of the 8 XCDs
+  const int64_t units = (int64_t)a.n_trig * a.Hkv;
+  if (units == 0) return hipSuccess;
+  a.parts = 1;
+  while ((units * a.parts) & 7) a.parts *= 2;
+  a.rb_part = (a.n_rb + a.parts - 1) / a.parts;
+  a.n_blocks = units * a.parts * a.rb_part;
   hipLaunchKernelGGL((attn_kernel<D, QT>), dim3((unsigned)a.n_blocks), dim3(kAttnThreads), 0, stream, a);
   return hipGetLastError();
+}
+
+// One workgroup occupies a CU (its LDS ring).  A 128-row workgroup (one
+// 16-row tile per wave) takes three quarters of a 256-row one's time, so it
+// wins only where all of them run at once: 1 x 768 tokens over 1200 cached,
+// 32/8 heads, 68 -> 51 us (192 workgroups instead of 96); 3 x 700 tokens, 96 us
+// with 264 large workgroups against 106 us with 528 small ones.
+template <int D>
+hipError_t launch_attn(const AttnArgs& a, hipStream_t stream) {
+  const int64_t units = (int64_t)a.n_trig * a.Hkv, rows = (int64_t)a.G * a.W;
+  if (units * ((rows + ACfg<D, 1>::kRowsWG - 1) / ACfg<D, 1>::kRowsWG) <= kCUs) return launch_attn_t<D, 1>(a, stream);
+  return launch_attn_t<D, 2>(a, stream);
 }
 
 }  // namespace
@@ -501,8 +550,8 @@ hipError_t launch_recompute_attention(const Geom& g, const void* q, const void* 
   a.win_start = win_start;
   a.status = status;
   a.out = (char*)out;
-  if (g.d == 128) return launch_attn_t<128, 2>(a, stream);
-  return launch_attn_t<64, 2>(a, stream);
+  if (g.d == 128) return launch_attn<128>(a, stream);
+  return launch_attn<64>(a, stream);
 }
 
 }  // namespace kara

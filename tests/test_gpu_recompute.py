@@ -118,6 +118,37 @@ def test_attention_parity(window, n_q, n_kv, d, bs, prefix):
     print(f"[case] ok, max abs err {worst:.2e}", flush=True)
 
 
+@pytest.mark.parametrize("n_seqs,window,n_q,n_kv,d", [
+    (1, 129, 4, 1, 128),      # one unit: eight pieces, most of them empty; 128-row workgroups
+    (5, 70, 6, 2, 64),        # ten units: four pieces each; ranks by length
+    (7, 280, 16, 4, 128),     # 28 units: two pieces, 128-row workgroups on 252 of 256 CUs ...
+    (7, 280, 20, 5, 128),     # ... and 256-row workgroups past them (35 units, eight pieces)
+    (3, 600, 32, 8, 128),     # 24 units: whole units, an uneven last row block
+])
+def test_attention_block_dealing(n_seqs, window, n_q, n_kv, d):
+    # every row block of every unit is computed once, whatever the pieces and
+    # the rank order: the parity bound of the file header, all sequences
+    import kara_check as kc
+    from paper_2607_01237_amd import kara
+    _need_gpu()
+    print(f"\n[case] attention dealing {n_seqs} x W={window} {n_q}/{n_kv} d={d}", flush=True)
+    geom, p, q, kp, vp, trig, bt, lens, ws = _setup(n_seqs, window, n_q, n_kv, d, 16, (0, 400), seed=3)
+    params = kara.make_params(p, geom.block_table.shape[0])
+    trig = trig.flip(0).contiguous()
+    out = torch.full_like(q, float("nan"))
+    status = torch.full((n_seqs,), -7, dtype=torch.int32, device=q.device)
+    kara.recompute_attention(params, trig, q, kp, vp, bt, lens, ws, out, status)
+    torch.cuda.synchronize()
+    assert (status.cpu().numpy() == 0).all()
+    geom.trig = geom.trig[::-1].copy()
+    got = to_f64(ki.raw_numpy(out), "bf16")
+    q_h, kp_h, vp_h = ki.raw_numpy(q), ki.raw_numpy(kp), ki.raw_numpy(vp)
+    for t in range(n_seqs):
+        want, spread = _oracle_attention(geom, p, q_h, kp_h, vp_h, t, with_spread=True)
+        kc.check_attention(got[t], want, spread, f"trigger {t}")
+    print("[case] ok", flush=True)
+
+
 def test_attention_flags_bad_windows():
     from paper_2607_01237_amd import kara
     _need_gpu()
