@@ -25,7 +25,8 @@ extern "C" {
 
 /* Query heads per KV head the decode attention supports. */
 #define KARA_HARNESS_MAX_GROUP 16
-/* Keys per split of the decode attention. */
+/* Keys per split of the decode attention, at least (the workspace is sized
+ * for this many; large launches use longer splits). */
 #define KARA_HARNESS_SPLIT_KEYS 256
 
 /*

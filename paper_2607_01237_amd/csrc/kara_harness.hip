@@ -3,6 +3,7 @@
 // per (layer, sequence, query head) over the compressed cache.  Not part of
 // the compression step; same paged layout.
 #include <cmath>
+#include <type_traits>
 
 #include "kara_harness.h"
 #include "kara_internal.h"
@@ -16,6 +17,7 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kNegInf = -__builtin_huge_valf();
 constexpr int kSplitKeys = KARA_HARNESS_SPLIT_KEYS;
+constexpr int kDecWgTarget = 4096;   // workgroups a launch keeps when its splits grow (16 per CU)
 
 // ---------------------------------------------------------------- append
 
@@ -84,59 +86,86 @@ __global__ void append_commit_kernel(int n, const int32_t* __restrict__ seqs, in
 
 // ---------------------------------------------------------------- decode
 
-// A lane's MFMA operand for 16-row tiles: lane group gq = lane/16 supplies
-// head-dim elements [gq*d/4, (gq+1)*d/4) of row lane%16.
-template <int DT, int D>
-struct Op16 {
-  static constexpr int kChunks = (D * (DT == KARA_BF16 ? 2 : 4) / 16) / 4;
-  uint4 v[kChunks];
+constexpr int kDecThreads = 256;
+constexpr int kDecWaves = kDecThreads / 64;
+constexpr int kDecMaxSplit = 1024;   // keys per split, at most
+
+// Geometry of one instance: element type DT, head dim D, GP query heads.
+template <int DT, int D, int GP>
+struct DCfg {
+  static constexpr int kES = DT == KARA_BF16 ? 2 : 4;
+  static constexpr int kRowBytes = D * kES;
+  // 16-key tiles per block, and buffers of its keys: what fits the registers
+  // of two waves per SIMD
+  static constexpr int kTB = DT == KARA_BF16 && (GP < 16 || D == 64) ? 2 : 1;
+  static constexpr int kKBuf = DT == KARA_F32 && D == 128 && GP == 16 ? 1 : 2;
+  static constexpr int kBlock = 16 * kTB;                  // keys per block
+  static constexpr int kKC = kRowBytes / 64;               // 16-byte chunks of a key row per lane
+  static constexpr int kE = D / 16;                        // output columns per lane
+  static constexpr int kVBytes = kE * kES;                 // a lane's bytes of a value row: 8, 16 or 32
+  static constexpr int kVW = kVBytes / 4;
 };
 
-template <int DT, int D>
-__device__ inline floatx4 dot16(const Op16<DT, D>& a, const Op16<DT, D>& b) {
-  floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-  if constexpr (DT == KARA_BF16) {
-#pragma unroll
-    for (int s = 0; s < Op16<DT, D>::kChunks; ++s) {
-      bf16x8 x, y;
-      __builtin_memcpy(&x, &a.v[s], 16);
-      __builtin_memcpy(&y, &b.v[s], 16);
-      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, y, acc, 0, 0, 0);
-    }
-  } else {
-    const float* x = (const float*)a.v;
-    const float* y = (const float*)b.v;
-#pragma unroll
-    for (int s = 0; s < Op16<DT, D>::kChunks * 4; ++s) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[s], y[s], acc, 0, 0, 0);
-  }
-  return acc;
+// p of lane `I` of the 16-lane row, in every lane of the row
+template <int I>
+__device__ __forceinline__ float row_bcast(float p) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, p), 0x150 + I, 0xf, 0xf, false));
 }
 
-__device__ inline float to_f32(const char* p, int dtype) {
-  if (dtype == KARA_BF16) {
-    const uint32_t b = *(const uint16_t*)p;
-    return __uint_as_float(b << 16);
+template <int B, int E, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (B < E) {
+    f(std::integral_constant<int, B>{});
+    static_for<B + 1, E>(f);
   }
-  return *(const float*)p;
 }
 
-// One wave per (layer, sequence, KV head, split of kSplitKeys keys): for the
-// G query heads of the KV head, the split's running maximum m, exponential
-// sum l and unnormalised output o (log2 units; partial softmax of the split).
-// Workspace record per (layer, j, query head, split): m, l, o[d].
-template <int DT, int D>
-__global__ __launch_bounds__(64) void decode_split_kernel(Geom g, int n, const int32_t* __restrict__ seqs,
-                                                          const char* __restrict__ q, PoolPtrs kp, PoolPtrs vp,
-                                                          const int32_t* __restrict__ bt,
-                                                          const int32_t* __restrict__ seq_lens, int max_len,
-                                                          int n_splits, float* __restrict__ ws) {
-  constexpr int ES = DT == KARA_BF16 ? 2 : 4;
-  constexpr int kRowBytes = D * ES;
-  constexpr int KC = Op16<DT, D>::kChunks;
-  constexpr int kDPerLane = D / 64;
-  __shared__ float p_tile[16][16];   // probabilities of the tile: [query head][key]
+// sums over the four 16-lane rows, of two values at once: row 0/1 lanes end
+// with a's sum, row 2/3 lanes with b's
+__device__ __forceinline__ float swap32_add(float a, float b) {
+  const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(s[0]) + __uint_as_float(s[1]);
+}
+__device__ __forceinline__ float swap16_add(float a, float b) {
+  const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(s[0]) + __uint_as_float(s[1]);
+}
 
-  const int lane = threadIdx.x;
+// One workgroup of four waves per (layer, sequence, KV head, split of
+// split_keys keys): for the KV head's G query heads, the split's maximum m,
+// exponential sum l and unnormalised output o, in log2 units and fp32.
+//
+// Bound by the K and V bytes.  The rows' pool offsets are formed once per
+// split into LDS, so no load waits on the block table, and the waves take
+// the split's 32-key blocks (16 in fp32) in turn, each with the next block's
+// keys and this block's values in flight while it works: about 20 KB per
+// wave.  S^T = K Q^T on the matrix cores puts query li of lane (gq, li)
+// against keys 16t + 4gq + r, and the value rows are loaded so that row gq of
+// the wave holds exactly those keys: a weight reaches the 16 lanes that hold
+// its key's columns by one DPP row broadcast, and P V runs in fp32 on the
+// vector units (about a quarter of the time the bytes take), with no LDS
+// exchange.  The reference m is raised only past a headroom of 2^8.
+// 128 sequences x 4 layers of 8K tokens, 40/8 heads, bf16 (15.9 GB): 8.0 ms
+// with one wave per 256 keys and loads that waited on the table, 2.8 ms here
+// (5.6 TB/s); 8 sequences of 300-4000 tokens, one layer: 138 -> 21 us.
+//
+// One split in the launch, or a sequence that ends inside its first: out
+// is written here.  Otherwise a record per (layer, j, query head, split) in
+// ws, strided as n_splits: m, l, o[d].
+template <int DT, int D, int GP>
+__global__ __launch_bounds__(kDecThreads, 2) void decode_split_kernel(
+    Geom g, int n, const int32_t* __restrict__ seqs, const char* __restrict__ q, PoolPtrs kp, PoolPtrs vp,
+    const int32_t* __restrict__ bt, const int32_t* __restrict__ seq_lens, int max_len, int split_keys, int n_splits,
+    float* __restrict__ ws, float* __restrict__ out) {
+  using C = DCfg<DT, D, GP>;
+  constexpr int TB = C::kTB, KC = C::kKC, E = C::kE, VW = C::kVW;
+  __shared__ __attribute__((aligned(16))) uint32_t row_of[kDecMaxSplit];   // pool row of the split's keys
+  __shared__ __attribute__((aligned(16))) float red_o[kDecWaves][GP][D];
+  __shared__ float red_m[kDecWaves][16], red_l[kDecWaves][16];
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int gq = lane >> 4, li = lane & 15;
   const int split = blockIdx.x % n_splits;
   const int64_t rest = blockIdx.x / n_splits;
@@ -144,127 +173,233 @@ __global__ __launch_bounds__(64) void decode_split_kernel(Geom g, int n, const i
   const int j = (int)((rest / g.Hkv) % n);
   const int l = (int)(rest / ((int64_t)g.Hkv * n));
   const int s = seqs[j];
-  if (s < 0 || s >= g.n_seqs) return;   // the combine kernel writes its zero rows
-  const int len = seq_lens[s];
-  const int k0 = split * kSplitKeys;
-  if (len <= 0 || len > max_len || k0 >= len) return;
-  const int k1 = min(len, k0 + kSplitKeys);
   const int G = g.G;
+  const int64_t orow = ((int64_t)l * n + j) * g.Hq + h * G;   // first query head's output row
+  const int len = s >= 0 && s < g.n_seqs ? seq_lens[s] : 0;
+  const int k0 = split * split_keys;
+  if (len <= 0 || len > max_len || k0 >= len) {
+    // no keys: zero rows where no combine kernel follows
+    if (n_splits == 1)
+      for (int i = tid; i < G * D; i += kDecThreads) out[orow * D + i] = 0.f;
+    return;
+  }
+  const int nk = min(len - k0, split_keys);                   // keys of this split
   const float c = g.scale * kLog2e;
 
-  // query rows (row r < G is query head h*G + r; others zero)
-  Op16<DT, D> qa;
   {
-    const int r = li;
-    const uint4* src = (const uint4*)(q + (((int64_t)l * n + j) * g.Hq + h * G + (r < G ? r : 0)) * kRowBytes) + gq * KC;
-#pragma unroll
-    for (int x = 0; x < KC; ++x) qa.v[x] = r < G ? src[x] : uint4{0, 0, 0, 0};
+    const int32_t* row_pages = bt + (int64_t)s * g.max_blocks;
+    // (padding keys of the last block repeat its last key, with no weight)
+    const int npad = (nk + C::kBlock - 1) / C::kBlock * C::kBlock;
+    for (int i = tid; i < npad; i += kDecThreads) {
+      const int pos = k0 + min(i, nk - 1);
+      const int b = pos / g.bs;
+      row_of[i] = (uint32_t)(((int64_t)row_pages[b] * g.Hkv + h) * g.bs + (pos - b * g.bs));
+    }
   }
-  const int32_t* row_pages = bt + (int64_t)s * g.max_blocks;
-  const char* kbase = (const char*)kp.p[l];
-  const char* vbase = (const char*)vp.p[l];
+  // lane (gq, li): 16-byte chunks gq + 4x of row li (any assignment of chunks
+  // to lane groups gives the same dot product; this one makes each load
+  // instruction read 64 contiguous bytes of a row)
+  uint4 qa[KC];
+  {
+    const uint4* src = (const uint4*)(q + (orow + (li < G ? li : 0)) * C::kRowBytes) + gq;
+#pragma unroll
+    for (int x = 0; x < KC; ++x) qa[x] = li < G ? src[4 * x] : uint4{0, 0, 0, 0};
+  }
+  __syncthreads();
 
-  // per-row state, held in lanes gq = r/4 (element r%4) for the softmax and
-  // replicated into every lane for the output
-  float m[4] = {kNegInf, kNegInf, kNegInf, kNegInf}, lsum[4] = {0.f, 0.f, 0.f, 0.f};
-  float o[16][kDPerLane];
-  float mo[16];   // each row's running maximum, as every lane sees it
+  const char* kbase = (const char*)kp.p[l] + gq * 16;
+  const char* vbase = (const char*)vp.p[l] + li * (C::kVBytes < 16 ? C::kVBytes : 16);
+  uint4 kb[C::kKBuf][TB][KC];
+  uint32_t vb[TB][4][VW];
+  auto load_k = [&](int blk, int b) __attribute__((always_inline)) {
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    mo[r] = kNegInf;
+    for (int t = 0; t < TB; ++t) {
+      const char* src = kbase + (uint64_t)row_of[blk * C::kBlock + t * 16 + li] * C::kRowBytes;
 #pragma unroll
-    for (int e = 0; e < kDPerLane; ++e) o[r][e] = 0.f;
+      for (int x = 0; x < KC; ++x) kb[b][t][x] = *(const uint4*)(src + x * 64);
+    }
+  };
+  auto load_v = [&](int blk) __attribute__((always_inline)) {
+#pragma unroll
+    for (int t = 0; t < TB; ++t) {
+      const uint4 rows = *(const uint4*)&row_of[blk * C::kBlock + t * 16 + 4 * gq];
+      const uint32_t rw[4] = {rows.x, rows.y, rows.z, rows.w};
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const char* src = vbase + (uint64_t)rw[r] * C::kRowBytes;
+        if constexpr (VW == 2) {
+          const uint2 v = *(const uint2*)src;
+          vb[t][r][0] = v.x, vb[t][r][1] = v.y;
+        } else {
+          // (32 bytes per lane: columns 4li.. and 64 + 4li..)
+#pragma unroll
+          for (int y = 0; y < VW / 4; ++y) {
+            const uint4 v = *(const uint4*)(src + y * 256);
+            vb[t][r][4 * y] = v.x, vb[t][r][4 * y + 1] = v.y, vb[t][r][4 * y + 2] = v.z, vb[t][r][4 * y + 3] = v.w;
+          }
+        }
+      }
+    }
+  };
+
+  float m = kNegInf, lsum = 0.f;   // query li's reference, and this lane's part of its sum
+  float o[GP][E];                  // query i, this lane's columns, over its row's keys
+#pragma unroll
+  for (int i = 0; i < GP; ++i)
+#pragma unroll
+    for (int e = 0; e < E; ++e) o[i][e] = 0.f;
+
+  const int nblk = (nk + C::kBlock - 1) / C::kBlock;
+  auto work = [&](int blk, int b) __attribute__((always_inline)) {
+    floatx4 sv[TB];
+#pragma unroll
+    for (int t = 0; t < TB; ++t) {
+      floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int x = 0; x < KC; ++x) {
+        if constexpr (DT == KARA_BF16) {
+          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kb[b][t][x]),
+                                                        __builtin_bit_cast(bf16x8, qa[x]), acc, 0, 0, 0);
+        } else {
+          const floatx4 ka = __builtin_bit_cast(floatx4, kb[b][t][x]), qx = __builtin_bit_cast(floatx4, qa[x]);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(ka[i], qx[i], acc, 0, 0, 0);
+        }
+      }
+      sv[t] = acc;
+    }
+    const int left = nk - blk * C::kBlock;
+    if (left < C::kBlock) {
+#pragma unroll
+      for (int t = 0; t < TB; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (t * 16 + 4 * gq + r >= left) {
+            sv[t][r] = kNegInf;
+#pragma unroll
+            for (int x = 0; x < VW; ++x) vb[t][r][x] = 0;   // its weight is 0, its value must be finite
+          }
+    }
+    float mx = sv[0][0];
+#pragma unroll
+    for (int t = 0; t < TB; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) mx = fmaxf(mx, sv[t][r]);
+    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * c;
+    if (__ballot(mx > m + 8.f) != 0ull) {
+      const float mn = fmaxf(m, mx);
+      const float f = m == kNegInf ? 0.f : __builtin_amdgcn_exp2f(m - mn);
+      m = mn;
+      lsum *= f;
+      static_for<0, GP>([&](auto i) __attribute__((always_inline)) {
+        const float fi = row_bcast<decltype(i)::value>(f);
+#pragma unroll
+        for (int e = 0; e < E; ++e) o[decltype(i)::value][e] *= fi;
+      });
+    }
+#pragma unroll
+    for (int t = 0; t < TB; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float p = __builtin_amdgcn_exp2f(fmaf(sv[t][r], c, -m));
+        lsum += p;
+        float v[E];
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+          if constexpr (DT == KARA_BF16)
+            v[e] = __uint_as_float((e & 1) ? vb[t][r][e >> 1] & 0xffff0000u : vb[t][r][e >> 1] << 16);
+          else
+            v[e] = __uint_as_float(vb[t][r][e]);
+        }
+        static_for<0, GP>([&](auto i) __attribute__((always_inline)) {
+          const float pi = row_bcast<decltype(i)::value>(p);
+#pragma unroll
+          for (int e = 0; e < E; ++e) o[decltype(i)::value][e] = fmaf(pi, v[e], o[decltype(i)::value][e]);
+        });
+      }
+  };
+  // (next block's keys after this block's values, so that waiting for the
+  // values leaves the keys in flight)
+  if constexpr (C::kKBuf == 1) {
+    for (int blk = wave; blk < nblk; blk += kDecWaves) {
+      load_k(blk, 0);
+      load_v(blk);
+      work(blk, 0);
+    }
+  } else if (wave < nblk) {
+    load_k(wave, 0);
+    int blk = wave;
+    for (;;) {
+      load_v(blk);
+      const int n1 = blk + kDecWaves;
+      if (n1 < nblk) load_k(n1, 1);
+      work(blk, 0);
+      if (n1 >= nblk) break;
+      load_v(n1);
+      blk = n1 + kDecWaves;
+      if (blk < nblk) load_k(blk, 0);
+      work(n1, 1);
+      if (blk >= nblk) break;
+    }
   }
 
-  for (int t0 = k0; t0 < k1; t0 += 16) {
-    const int key = t0 + li;
-    Op16<DT, D> kb;
-    if (key < k1) {
-      const int64_t pg = row_pages[key / g.bs];
-      const uint4* src = (const uint4*)(kbase + ((pg * g.Hkv + h) * g.bs + key % g.bs) * kRowBytes) + gq * KC;
+  // ---- the wave's sums over its four rows, then the four waves' ----
+  lsum = swap32_add(lsum, lsum);
+  lsum = swap16_add(lsum, lsum);
+  if (gq == 0) {
+    red_m[wave][li] = m;
+    red_l[wave][li] = lsum;
+  }
+  // columns of a lane: bf16 E*li + e; fp32 at d = 128 4li + e and 64 + 4li + e - 4
+  auto column = [&](int e) { return DT == KARA_F32 && E == 8 ? (e >> 2) * 64 + 4 * li + (e & 3) : E * li + e; };
 #pragma unroll
-      for (int x = 0; x < KC; ++x) kb.v[x] = src[x];
+  for (int i = 0; i < GP; ++i)
+#pragma unroll
+    for (int e = 0; e < E; e += 4) {
+      // rows 0..3 of the wave end with columns e, e+1, e+2, e+3
+      const float x0 = swap32_add(o[i][e], o[i][e + 2]);
+      const float x1 = swap32_add(o[i][e + 1], o[i][e + 3]);
+      const float y = swap16_add(x0, x1);
+      // (the 32-lane swap leaves a in rows 0,1 and b in rows 2,3; the 16-lane
+      // one a in rows 0,2 and b in rows 1,3)
+      red_o[wave][i][column(e + (gq >> 1) * 2 + (gq & 1))] = y;
+    }
+  __syncthreads();
+  const int nw = min(nblk, kDecWaves);   // waves that had keys
+  const bool direct = len <= split_keys;
+  float* rec = ws + (orow * n_splits + split) * (D + 2);
+  for (int x = tid; x < G * D; x += kDecThreads) {
+    const int i = x / D, e = x - i * D;
+    float M = red_m[0][i];
+    for (int w = 1; w < nw; ++w) M = fmaxf(M, red_m[w][i]);
+    float L = 0.f, O = 0.f;
+    for (int w = 0; w < nw; ++w) {
+      const float f = __builtin_amdgcn_exp2f(red_m[w][i] - M);
+      L += red_l[w][i] * f;
+      O += red_o[w][i][e] * f;
+    }
+    if (direct) {
+      out[orow * D + x] = O / L;
     } else {
-#pragma unroll
-      for (int x = 0; x < KC; ++x) kb.v[x] = uint4{0, 0, 0, 0};
+      float* r = rec + (int64_t)i * n_splits * (D + 2);
+      if (e == 0) r[0] = M, r[1] = L;
+      r[2 + e] = O;
     }
-    const floatx4 sc = dot16<DT, D>(qa, kb);   // rows 4*gq+e, key li
-    // running maximum and sum per row (lanes of one lane group share rows)
-    float pv[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const float x = key < k1 ? sc[e] * c : kNegInf;
-      float tm = x;
-#pragma unroll
-      for (int off = 1; off < 16; off <<= 1) tm = fmaxf(tm, __shfl_xor(tm, off, 64));
-      const float mn = fmaxf(m[e], tm);
-      const float p = key < k1 ? __builtin_amdgcn_exp2f(x - mn) : 0.f;
-      float ps = p;
-#pragma unroll
-      for (int off = 1; off < 16; off <<= 1) ps += __shfl_xor(ps, off, 64);
-      lsum[e] = lsum[e] * (m[e] == kNegInf ? 0.f : __builtin_amdgcn_exp2f(m[e] - mn)) + ps;
-      m[e] = mn;
-      pv[e] = p;
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) p_tile[4 * gq + e][li] = pv[e];
-    __syncthreads();
-    // o[r] = o[r] * 2^(m_old - m_new) + sum_k p[r][k] v_k; lane owns head-dim
-    // elements lane*kDPerLane..
-    float vrow[16][kDPerLane];
-#pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      const int kx = t0 + kk;
-      if (kx < k1) {
-        const int64_t pg = row_pages[kx / g.bs];
-        const char* vr = vbase + ((pg * g.Hkv + h) * g.bs + kx % g.bs) * kRowBytes + lane * kDPerLane * ES;
-#pragma unroll
-        for (int e = 0; e < kDPerLane; ++e) vrow[kk][e] = to_f32(vr + e * ES, DT);
-      } else {
-#pragma unroll
-        for (int e = 0; e < kDPerLane; ++e) vrow[kk][e] = 0.f;
-      }
-    }
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      if (r >= G) break;
-      const float mn = __shfl(m[r & 3], (r >> 2) * 16, 64);
-      const float f = mo[r] == kNegInf ? 0.f : __builtin_amdgcn_exp2f(mo[r] - mn);
-      mo[r] = mn;
-#pragma unroll
-      for (int e = 0; e < kDPerLane; ++e) {
-        float acc = o[r][e] * f;
-#pragma unroll
-        for (int kk = 0; kk < 16; ++kk) acc = fmaf(p_tile[r][kk], vrow[kk][e], acc);
-        o[r][e] = acc;
-      }
-    }
-    __syncthreads();
-  }
-  // records: m, l, o[d]
-  const int rec = D + 2;
-  for (int r = 0; r < G; ++r) {
-    float* w = ws + ((((int64_t)l * n + j) * g.Hq + h * G + r) * n_splits + split) * rec;
-    const float mr = __shfl(m[r & 3], (r >> 2) * 16, 64);
-    const float lr = __shfl(lsum[r & 3], (r >> 2) * 16, 64);
-    if (lane == 0) {
-      w[0] = mr;
-      w[1] = lr;
-    }
-#pragma unroll
-    for (int e = 0; e < kDPerLane; ++e) w[2 + lane * kDPerLane + e] = o[r][e];
   }
 }
 
-// One wave per (layer, sequence, query head): combine the splits.
+// One wave per (layer, sequence, query head) of a sequence longer than one
+// split: its splits' records combined, eight in flight at a time.
 template <int D>
-__global__ __launch_bounds__(64) void decode_combine_kernel(Geom g, int n, const int32_t* __restrict__ seqs,
-                                                            const int32_t* __restrict__ seq_lens, int max_len,
-                                                            int n_splits, const float* __restrict__ ws,
-                                                            float* __restrict__ out) {
+__global__ __launch_bounds__(256) void decode_combine_kernel(Geom g, int n, const int32_t* __restrict__ seqs,
+                                                             const int32_t* __restrict__ seq_lens, int max_len,
+                                                             int split_keys, int n_splits, int64_t n_rows,
+                                                             const float* __restrict__ ws, float* __restrict__ out) {
   constexpr int kDPerLane = D / 64;
-  const int lane = threadIdx.x;
-  const int64_t row = blockIdx.x;                 // (l, j, hq)
+  const int lane = threadIdx.x & 63;
+  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);   // (l, j, hq)
+  if (row >= n_rows) return;
   const int j = (int)((row / g.Hq) % n);
   const int s = seqs[j];
   const int len = s >= 0 && s < g.n_seqs ? seq_lens[s] : 0;
@@ -274,34 +409,74 @@ __global__ __launch_bounds__(64) void decode_combine_kernel(Geom g, int n, const
     for (int e = 0; e < kDPerLane; ++e) dst[e] = 0.f;
     return;
   }
-  const int ns = (len + kSplitKeys - 1) / kSplitKeys;
+  if (len <= split_keys) return;   // the split kernel wrote it
+  const int ns = (len + split_keys - 1) / split_keys;
   const int rec = D + 2;
   const float* w = ws + row * n_splits * rec;
+  // lane i: split i's maximum and sum (64 at a time)
   float M = kNegInf;
-  for (int sp = 0; sp < ns; ++sp) M = fmaxf(M, w[sp * rec]);
-  float L = 0.f, acc[kDPerLane] = {};
-  for (int sp = 0; sp < ns; ++sp) {
-    const float f = __builtin_amdgcn_exp2f(w[sp * rec] - M);
-    L += w[sp * rec + 1] * f;
+  for (int sp = lane; sp < ns; sp += 64) M = fmaxf(M, w[sp * rec]);
 #pragma unroll
-    for (int e = 0; e < kDPerLane; ++e) acc[e] += w[sp * rec + 2 + lane * kDPerLane + e] * f;
+  for (int x = 1; x < 64; x <<= 1) M = fmaxf(M, __shfl_xor(M, x, 64));
+  float L = 0.f, acc[kDPerLane] = {};
+  for (int sp0 = 0; sp0 < ns; sp0 += 64) {
+    const int sp = sp0 + lane;
+    const float f = sp < ns ? __builtin_amdgcn_exp2f(w[sp * rec] - M) : 0.f;
+    const float lf = sp < ns ? w[sp * rec + 1] * f : 0.f;
+    const int cnt = min(64, ns - sp0);
+#pragma unroll 8
+    for (int i = 0; i < cnt; ++i) {
+      L += __shfl(lf, i, 64);
+      const float fi = __shfl(f, i, 64);
+#pragma unroll
+      for (int e = 0; e < kDPerLane; ++e) acc[e] += w[(sp0 + i) * rec + 2 + lane * kDPerLane + e] * fi;
+    }
   }
 #pragma unroll
   for (int e = 0; e < kDPerLane; ++e) dst[e] = acc[e] / L;
 }
 
+// Keys per split: 256 (the workspace's records are sized for that) while
+// the launch has few workgroups, up to 1024 where 16 per CU remain: fewer
+// records and prologues.
+int decode_split_keys(const Geom& g, int n, int n_layers, int max_len) {
+  const int64_t units = (int64_t)n_layers * n * g.Hkv;
+  int keys = kSplitKeys;
+  while (keys < kDecMaxSplit && units * ((max_len + 2 * keys - 1) / (2 * keys)) >= kDecWgTarget) keys *= 2;
+  return keys;
+}
+
+template <int DT, int D, int GP>
+hipError_t launch_decode_g(const Geom& g, int n, const int32_t* seqs, int n_layers, const void* q, const PoolPtrs& kp,
+                           const PoolPtrs& vp, const int32_t* bt, const int32_t* seq_lens, int max_len, float* out,
+                           float* ws, hipStream_t stream) {
+  const int keys = decode_split_keys(g, n, n_layers, max_len);
+  const int n_splits = (max_len + keys - 1) / keys;
+  const int64_t blocks = (int64_t)n_layers * n * g.Hkv * n_splits;
+  hipLaunchKernelGGL((decode_split_kernel<DT, D, GP>), dim3((unsigned)blocks), dim3(kDecThreads), 0, stream, g, n, seqs,
+                     (const char*)q, kp, vp, bt, seq_lens, max_len, keys, n_splits, ws, out);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || n_splits == 1) return e;
+  const int64_t rows = (int64_t)n_layers * n * g.Hq;
+  hipLaunchKernelGGL((decode_combine_kernel<D>), dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, stream, g, n, seqs,
+                     seq_lens, max_len, keys, n_splits, rows, (const float*)ws, out);
+  return hipGetLastError();
+}
+
+// query heads per KV head, rounded up to an instance's accumulators
 template <int DT, int D>
 hipError_t launch_decode(const Geom& g, int n, const int32_t* seqs, int n_layers, const void* q, const PoolPtrs& kp,
                          const PoolPtrs& vp, const int32_t* bt, const int32_t* seq_lens, int max_len, float* out,
-                         float* ws, int n_splits, hipStream_t stream) {
-  const int64_t blocks = (int64_t)n_layers * n * g.Hkv * n_splits;
-  hipLaunchKernelGGL((decode_split_kernel<DT, D>), dim3((unsigned)blocks), dim3(64), 0, stream, g, n, seqs,
-                     (const char*)q, kp, vp, bt, seq_lens, max_len, n_splits, ws);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((decode_combine_kernel<D>), dim3((unsigned)((int64_t)n_layers * n * g.Hq)), dim3(64), 0,
-                     stream, g, n, seqs, seq_lens, max_len, n_splits, (const float*)ws, out);
-  return hipGetLastError();
+                         float* ws, hipStream_t stream) {
+#define KARA_DECODE_G(GP) \
+  return launch_decode_g<DT, D, GP>(g, n, seqs, n_layers, q, kp, vp, bt, seq_lens, max_len, out, ws, stream)
+  if (g.G == 1) KARA_DECODE_G(1);
+  if (g.G == 2) KARA_DECODE_G(2);
+  if (g.G <= 4) KARA_DECODE_G(4);
+  if (g.G == 5) KARA_DECODE_G(5);
+  if (g.G <= 8) KARA_DECODE_G(8);
+  KARA_DECODE_G(16);
+#undef KARA_DECODE_G
 }
 
 // the step's window fields are irrelevant here; validate the rest
@@ -385,20 +560,19 @@ kara_status_t kara_harness_decode_attention(const kara_params_t* p, int32_t n, c
     kp.p[i] = const_cast<void*>(k_pools[i]);
     vp.p[i] = const_cast<void*>(v_pools[i]);
   }
-  const int n_splits = (max_len + kSplitKeys - 1) / kSplitKeys;
   hipStream_t s = (hipStream_t)stream;
   float* ws = (float*)workspace;
   hipError_t e;
   if (g.dtype == KARA_BF16)
     e = g.d == 128 ? launch_decode<KARA_BF16, 128>(g, n, seqs, n_layers, q, kp, vp, block_table, seq_lens, max_len,
-                                                  out, ws, n_splits, s)
+                                                  out, ws, s)
                    : launch_decode<KARA_BF16, 64>(g, n, seqs, n_layers, q, kp, vp, block_table, seq_lens, max_len,
-                                                 out, ws, n_splits, s);
+                                                 out, ws, s);
   else
     e = g.d == 128 ? launch_decode<KARA_F32, 128>(g, n, seqs, n_layers, q, kp, vp, block_table, seq_lens, max_len,
-                                                 out, ws, n_splits, s)
+                                                 out, ws, s)
                    : launch_decode<KARA_F32, 64>(g, n, seqs, n_layers, q, kp, vp, block_table, seq_lens, max_len,
-                                                out, ws, n_splits, s);
+                                                out, ws, s);
   return hip_status(e);
 }
 

@@ -98,6 +98,57 @@ def test_decode_attention(dtype, Hq, Hkv, d):
     print(f"[case] ok: max abs err {worst:.2e}", flush=True)
 
 
+@pytest.mark.parametrize("dtype,Hq,Hkv,d,n,L,bs,max_len", [
+    ("bf16", 8, 8, 64, 32, 8, 16, 1100),     # 2048 units: 1024-key splits, two of them, one query head each
+    ("f32", 4, 2, 64, 32, 24, 7, 1100),      # 1536 units: 512-key splits, 16-key blocks, odd pages
+    ("bf16", 6, 2, 128, 4, 1, 16, 1100),     # 8 units: 256-key splits, G = 3 of four accumulators
+    ("bf16", 16, 2, 128, 4, 1, 24, 800),     # G = 8
+    ("f32", 32, 2, 128, 4, 1, 16, 600),      # G = 16 in fp32: one buffer of keys
+    ("bf16", 8, 8, 64, 32, 24, 16, 200),     # one split: no combine, zero rows from the split kernel
+])
+def test_decode_splits(dtype, Hq, Hkv, d, n, L, bs, max_len):
+    # the split sizes (by units and max_len) and their edges: sequences that
+    # end inside the first split, at its end and one past it, partial 16-key
+    # tiles and 32-key blocks, an empty sequence, one over max_len.  Bound as
+    # above: fp32 logits are off by at most d 2^-24 sum |q k| / sqrt(d), about
+    # 2e-5 here, and an output by twice that times the largest value.
+    from paper_2607_01237_amd import kara
+    _need_gpu()
+    dev = torch.device("cuda:0")
+    rng = np.random.default_rng(n * 7 + d)
+    edges = [1, 15, 16, 17, 31, 33, 127, 129, 255, 256, 257, 511, 512, 513, 1023, 1024, 1025, max_len, max_len + 1, 0]
+    lens = np.array([min(edges[i % len(edges)], max_len + 1) for i in range(n)], dtype=np.int32)
+    if n < len(edges):
+        lens[:] = [257, max_len, 33, 512][:n]
+    p, table, _ = _geom(rng, n, Hq, Hkv, d, dtype, bs, lens, max_blocks=-(-(max_len + 1) // bs))
+    print(f"\n[case] decode splits {dtype} {Hq}/{Hkv} d={d} n={n} L={L} max_len={max_len}", flush=True)
+    params = kara.make_params(p, n)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator(device=dev).manual_seed(9)
+    R = lambda *shape: torch.randn(shape, generator=g, device=dev).to(dt)  # noqa: E731
+    kp, vp = ([R(p["num_pages"], Hkv, bs, d) for _ in range(L)] for _ in range(2))
+    q = R(L, n, Hq, d)
+    T = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(dev)  # noqa: E731
+    out = torch.full((L, n, Hq, d), float("nan"), dtype=torch.float32, device=dev)
+    ws = torch.full((kara.decode_workspace_size(params, n, L, max_len),), 255, dtype=torch.uint8, device=dev)
+    kara.decode_attention(params, T(np.arange(n, dtype=np.int32)), q, kp, vp, T(table), T(lens), max_len, out, ws)
+    torch.cuda.synchronize()
+    tab = T(table.astype(np.int64))
+    for l in (0, L - 1):
+        for j in range(n):
+            nt = int(lens[j])
+            if nt == 0 or nt > max_len:
+                assert (out[l, j] == 0).all(), f"seq {j} should give zero rows"
+                continue
+            pos = torch.arange(nt, device=dev)
+            K, V = (t[l][tab[j][pos // bs], :, pos % bs].double().permute(1, 0, 2).contiguous() for t in (kp, vp))
+            x = torch.matmul(q[l, j].double().view(Hkv, Hq // Hkv, d) / d ** 0.5, K.transpose(1, 2).contiguous())
+            want = torch.matmul(torch.softmax(x, dim=2), V).view(Hq, d)
+            err = (out[l, j].double() - want).abs()
+            assert bool((err <= 1e-4 + 1e-4 * want.abs()).all()), (l, j, nt, float(err.max()))
+    print("[case] ok", flush=True)
+
+
 @pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f32", 64)])
 def test_kv_append(dtype, d):
     from paper_2607_01237_amd import kara
