@@ -81,19 +81,24 @@ def parse():
 # on; a changed source makes the stored figure stale and the JSON reports null.
 
 TRAFFIC_SOURCES = {
-    "score": ["paper_2607_01237_amd/csrc/kara_score.hip"],
+    "score": ["paper_2607_01237_amd/csrc/kara_score.hip", "paper_2607_01237_amd/csrc/kara_score_res.hip",
+              "paper_2607_01237_amd/csrc/kara_score.h", "paper_2607_01237_amd/csrc/kara_score_dpp.h"],
     "select_compact": ["paper_2607_01237_amd/csrc/kara_select.hip", "paper_2607_01237_amd/csrc/kara_pages.hip"],
 }
-TRAFFIC_KERNELS = {"score": ["score1_kernel", "score_kernel", "split_sum_kernel"],
+TRAFFIC_KERNELS = {"score": ["score1_kernel", "score_kernel", "score_res_kernel", "split_sum_kernel"],
                    "select_compact": ["compact_kernel", "select_kernel"]}
 
 
 def scoring_kernel_name(p):
     """Which scoring kernel the library runs for these parameters (the rule
-    of its plan_score: the single-sweep kernel for bf16, d = 128 and
-    512 < N <= 2048 with pools and query blocks addressable by 32-bit
-    offsets; the two-sweep kernel otherwise)."""
+    of its plan_score: the resident-key kernel where the keys fit in LDS;
+    the single-sweep kernel for bf16, d = 128 and 512 < N <= 2048 with pools
+    and query blocks addressable by 32-bit offsets; the two-sweep kernel
+    otherwise)."""
     n = p["window"] - p["buffer"]
+    row = p["head_dim"] * (2 if p["dtype"] == "bf16" else 4)
+    if n <= {128: 1152, 256: 512, 512: 256}[row]:
+        return "score_res_kernel (resident-key window scoring, Eq. 4)"
     pool = p["num_pages"] * p["n_kv_heads"] * p["block_size"] * p["head_dim"] * 2
     qblk = (p.get("score_queries") or p["window"]) * p["n_q_heads"] * p["head_dim"] * 2
     if p["dtype"] == "bf16" and p["head_dim"] == 128 and 512 < n <= 2048 and pool < 2**32 and qblk < 2**32:

@@ -177,7 +177,9 @@ const char* kara_last_hip_error(void);
  * Bytes of device workspace kara_score_window / kara_compress_window need for
  * this geometry, n_trig triggered sequences and n_layers layers (written to
  * *bytes, a HOST pointer).  Holds partial column sums of Eq. (4) and, for
- * outputs the caller does not request, the scores and index sets.
+ * outputs the caller does not request, the scores and index sets.  The size
+ * also covers every launch of this geometry with fewer units (sequences x
+ * layers), so one workspace serves calls of any size up to it.
  */
 kara_status_t kara_workspace_size(const kara_params_t* p, int32_t n_trig, int32_t n_layers,
                                   size_t* bytes);
@@ -315,8 +317,9 @@ kara_status_t kara_compress_prefill(const kara_params_t* p, int32_t n_trig, cons
  * GPU it runs on until the process ends.  The call allocates nothing
  * (no hipMalloc, hipFree or allocating library routine).
  *
- * Limit: the workspace kara_workspace_size() reports for (p, n_trig,
- * n_layers) must fit in KARA_NOALLOC_SCRATCH_BYTES, else the call returns
+ * Limit: the scratch of the call (at most what kara_workspace_size()
+ * reports for (p, n_trig, n_layers)) must fit in KARA_NOALLOC_SCRATCH_BYTES,
+ * else the call returns
  * KARA_ERR_SCRATCH_LIMIT and enqueues nothing.  64 MiB holds about 3,000
  * units of a 32/8-head, W = 1024 model with scores and index sets left to
  * the library (22 KB each): 53 sequences x 7 layers, or one layer of 380

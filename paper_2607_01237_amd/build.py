@@ -42,6 +42,7 @@ FILE_FLAGS = {
     # instructions; the accumulation registers hold the single-sweep
     # kernel's stored weights
     "kara_score.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+    "kara_score_res.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
 }
 # rocBLAS runs the recompute pass's plain matrix products
 LINK_LIBS = ["-L/opt/rocm/lib", "-lrocblas"]

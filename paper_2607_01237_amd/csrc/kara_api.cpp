@@ -87,12 +87,13 @@ struct WsLayout {
   size_t partials, scores, discrete, kept, total;
 };
 
-WsLayout ws_layout(const Geom& g, int n_layers, const ScorePlan& sp) {
+// partial_rows: rows of N partial column sums
+WsLayout ws_layout(const Geom& g, int n_layers, int64_t partial_rows) {
   const int64_t units = (int64_t)n_layers * g.n_trig * g.n_win * g.Hkv;
   WsLayout w{};
   size_t off = 0;
   w.partials = off;
-  off = align_up(off + (sp.n_splits > 1 ? (size_t)units * sp.n_splits * g.N * sizeof(float) : 0));
+  off = align_up(off + (size_t)partial_rows * g.N * sizeof(float));
   w.scores = off;
   off = align_up(off + (size_t)units * g.N * sizeof(float));
   w.discrete = off;
@@ -103,6 +104,11 @@ WsLayout ws_layout(const Geom& g, int n_layers, const ScorePlan& sp) {
   return w;
 }
 
+
+// the layout a launch of this plan uses
+WsLayout ws_layout(const Geom& g, int n_layers, const ScorePlan& sp) {
+  return ws_layout(g, n_layers, sp.n_splits > 1 ? (int64_t)n_layers * g.n_trig * g.n_win * g.Hkv * sp.n_splits : 0);
+}
 
 // Runs fn(layer0, count, pool-pointer structs) over chunks of at most
 // kMaxLayersPerLaunch layers.
@@ -239,8 +245,8 @@ kara_status_t kara_workspace_size(const kara_params_t* p, int32_t n_trig, int32_
   kara_status_t st = make_geom(p, n_trig, &g);
   if (st != KARA_OK) return st;
   if (!bytes || n_layers < 1) return KARA_ERR_INVALID_ARG;
-  const ScorePlan sp = plan_score(g, (int64_t)n_layers * n_trig * g.Hkv);
-  *bytes = ws_layout(g, n_layers, sp).total;
+  // (enough for any smaller launch of this geometry too)
+  *bytes = ws_layout(g, n_layers, max_partial_rows(g, (int64_t)n_layers * n_trig * g.Hkv)).total;
   return KARA_OK;
 }
 

@@ -52,9 +52,14 @@ hipError_t launch_validate(const Geom& g, const int32_t* trig, const int32_t* bl
 struct ScorePlan {
   int rows_wg;          // query rows per workgroup
   int n_splits;         // row splits (workgroups) per unit
-  int single_nt;        // key tiles per wave of the single-sweep kernel; 0: two sweeps
+  int single_nt;        // key tiles per wave of the single-sweep kernel; 0: another one
+  bool resident;        // resident-key kernel
 };
 ScorePlan plan_score(const Geom& g, int64_t n_units);
+// The most partial rows (of N floats) a launch of up to n_units units of g
+// writes.  Launches of few units split their rows further, so this is what a
+// workspace sized for n_units must hold for a smaller launch to fit it too.
+int64_t max_partial_rows(const Geom& g, int64_t n_units);
 hipError_t launch_score(const Geom& g, const ScorePlan& sp, int n_layers, const void* q,
                         const PoolPtrs& k_pools, const int32_t* trig, const int32_t* block_table,
                         const int32_t* win_start, const int32_t* status, float* partials,
@@ -85,7 +90,7 @@ kara_status_t compress(const kara_params_t* p, int32_t n_trig, const int32_t* tr
                        int32_t* block_table, int32_t* seq_lens, const int32_t* win_start, int32_t commit,
                        float* scores, int32_t* discrete, int32_t* kept, int32_t* freed, int32_t* n_freed,
                        int32_t* status, void* workspace, size_t workspace_bytes, void* stream);
-// Workspace bytes compress() needs for g (g.n_trig, g.n_win set) and n_layers.
+// Workspace bytes compress() uses for g (g.n_trig, g.n_win set) and n_layers.
 size_t compress_workspace_bytes(const Geom& g, int32_t n_layers);
 
 // Window recompute pass (kara_attn.hip, kara_recompute_ops.hip).

@@ -2,10 +2,11 @@
 // per (sequence, layer, KV head), all G query heads of the group acting as
 // queries of their KV head.
 //
-// Two kernels.  score1_kernel (bf16, d = 128, 512 < N <= 2048, the shapes
+// Three kernels.  score1_kernel (bf16, d = 128, 512 < N <= 2048, the shapes
 // of the Qwen3-shaped workloads) forms and exponentiates every logit once,
 // holding each row block's weights in fp16 until the block's row sums are
-// known; it is described where it is defined.  score_kernel serves every
+// known; it is described where it is defined.  Windows whose keys fit in LDS
+// go to score_res_kernel (kara_score_res.hip).  score_kernel serves every
 // other shape with two sweeps over the keys:
 //
 // A workgroup of 8 waves owns 128*RT
@@ -29,9 +30,11 @@
 // split to finish would need a device-scope release/acquire, which on this
 // multi-XCD part writes back and invalidates the whole L2 of the XCD every
 // time.)  No floating-point atomics, so the scores are bit-reproducible.
+#include <algorithm>
 #include <type_traits>
 
-#include "kara_internal.h"
+#include "kara_score.h"
+#include "kara_score_dpp.h"
 
 namespace kara {
 namespace {
@@ -51,23 +54,6 @@ constexpr float kPosInf = __builtin_huge_valf();
 // Lower end of a running row maximum (log2 units): finite, so that
 // exp2(m_old - m_new) never sees inf - inf.
 constexpr float kMaxFloor = -1e30f;
-// Sweep A accumulates exp2(x - m) against a maximum m that is only raised
-// when a row sum would pass this bound, so no term or sum can overflow.
-constexpr float kSumBound = 18446744073709551616.f;   // 2^64
-
-struct ScoreArgs {
-  Geom g;
-  const char* q;              // [n_layers][n_trig][W][Hq][d]
-  PoolPtrs k;                 // per-layer K pools
-  const int32_t* trig;
-  const int32_t* bt;
-  const int32_t* win_start;
-  const int32_t* status;
-  float* partials;            // [units][n_splits][N] (unused with one split)
-  float* scores;              // [units][N]
-  int n_splits;
-  int64_t n_blocks;
-};
 
 // Static geometry of one kernel instance: element type DT, head dim D, RT
 // 16-row tiles per wave.
@@ -640,159 +626,6 @@ struct Score1Args {
 // the 16-byte chunk swizzle of a 256-byte row in LDS (conflict-free for the
 // operand reads: row's two low bits moved to the top)
 __device__ __forceinline__ int s1_swz(int row) { return ((row & 3) << 2) | ((row >> 2) & 3); }
-
-// Reductions over the 16 lanes of a row by DPP butterflies (quad swaps,
-// then half-row and row mirrors).  Every lane ends with the same value:
-// each step combines two equal partial results, in either order.
-template <class Op>
-__device__ __forceinline__ float dpp_reduce16(float v, Op op) {
-  v = op(v, __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0xB1, 0xF, 0xF, false)));
-  v = op(v, __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x4E, 0xF, 0xF, false)));
-  v = op(v, __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x141, 0xF, 0xF, false)));
-  v = op(v, __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x140, 0xF, 0xF, false)));
-  return v;
-}
-__device__ __forceinline__ float dpp_max16(float v) {
-  return dpp_reduce16(v, [](float x, float y) { return fmaxf(x, y); });
-}
-__device__ __forceinline__ float dpp_sum16(float v) {
-  return dpp_reduce16(v, [](float x, float y) { return x + y; });
-}
-
-// The same butterflies for 8 or 16 values at once, one DPP step over all of
-// them before the next (so no step reads a value written fewer than 8
-// instructions before; the leading s_nop covers the values' last writes
-// before the block).  Written as instructions because the compiler keeps a
-// separate DPP move per step, and in IEEE mode adds a quieting max before
-// every fmaxf.
-#define S1_DPP8(OP, PAT)                                                                               \
-  asm volatile("s_nop 1\n\t"                                                                           \
-               OP " %0, %0, %0 " PAT "\n\t" OP " %1, %1, %1 " PAT "\n\t" OP " %2, %2, %2 " PAT "\n\t"  \
-               OP " %3, %3, %3 " PAT "\n\t" OP " %4, %4, %4 " PAT "\n\t" OP " %5, %5, %5 " PAT "\n\t"  \
-               OP " %6, %6, %6 " PAT "\n\t" OP " %7, %7, %7 " PAT                                        \
-               : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]),     \
-                 "+v"(v[7]))
-#define S1_DPP16(OP, PAT)                                                                              \
-  asm volatile("s_nop 1\n\t"                                                                           \
-               OP " %0, %0, %0 " PAT "\n\t" OP " %1, %1, %1 " PAT "\n\t" OP " %2, %2, %2 " PAT "\n\t"  \
-               OP " %3, %3, %3 " PAT "\n\t" OP " %4, %4, %4 " PAT "\n\t" OP " %5, %5, %5 " PAT "\n\t"  \
-               OP " %6, %6, %6 " PAT "\n\t" OP " %7, %7, %7 " PAT "\n\t" OP " %8, %8, %8 " PAT "\n\t"  \
-               OP " %9, %9, %9 " PAT "\n\t" OP " %10, %10, %10 " PAT "\n\t" OP " %11, %11, %11 " PAT   \
-               "\n\t" OP " %12, %12, %12 " PAT "\n\t" OP " %13, %13, %13 " PAT "\n\t" OP " %14, %14, %14 " \
-               PAT "\n\t" OP " %15, %15, %15 " PAT                                                      \
-               : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]),     \
-                 "+v"(v[7]), "+v"(v[8]), "+v"(v[9]), "+v"(v[10]), "+v"(v[11]), "+v"(v[12]), "+v"(v[13]), \
-                 "+v"(v[14]), "+v"(v[15]))
-#define S1_DPP_ALL(M)                                                      \
-  if constexpr (MAX) {                                                     \
-    M("v_max_f32_dpp", "quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf");  \
-    M("v_max_f32_dpp", "quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf");  \
-    M("v_max_f32_dpp", "row_half_mirror row_mask:0xf bank_mask:0xf");      \
-    M("v_max_f32_dpp", "row_mirror row_mask:0xf bank_mask:0xf");           \
-  } else {                                                                 \
-    M("v_add_f32_dpp", "quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf");  \
-    M("v_add_f32_dpp", "quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf");  \
-    M("v_add_f32_dpp", "row_half_mirror row_mask:0xf bank_mask:0xf");      \
-    M("v_add_f32_dpp", "row_mirror row_mask:0xf bank_mask:0xf");           \
-  }
-template <bool MAX, int N>
-__device__ __forceinline__ void dpp_reduce16xn(float (&v)[N]) {
-  static_assert(N == 8 || N == 16, "8 or 16 values");
-  if constexpr (N == 16) {
-    S1_DPP_ALL(S1_DPP16)
-  } else {
-    S1_DPP_ALL(S1_DPP8)
-  }
-}
-#undef S1_DPP_ALL
-#undef S1_DPP16
-#undef S1_DPP8
-// Reduce-scatter over the 16 lanes of a row: every lane's v[i] combined,
-// lane li ending with index li's result.  Four butterfly steps, each
-// keeping half of the values: lanes li and li ^ 8 (a rotation by 8), then
-// li and 7 - li within each half (the half mirror), then the quad swaps
-// li ^ 2 and li ^ 1.  A lane keeps the half its bit names and sends the
-// other, so each step combines only the values that stay: 45 instructions
-// against 64 for every lane's full result.
-// (each step is one asm statement that starts with the wait states a DPP
-// read needs after the VALU writes of its sources, which all precede it)
-template <bool MAX, int K, int PATTERN>
-__device__ __forceinline__ void s1_rs_step(float (&keep)[8], const float (&send)[8]) {
-  // PATTERN: 0 row_ror:8, 1 row_half_mirror, 2 quad_perm:[2,3,0,1], 3 quad_perm:[1,0,3,2]
-#define S1_OPS(OP, PAT)                                                                                     \
-  if constexpr (K == 8)                                                                                     \
-    asm volatile("s_nop 1\n\t"                                                                              \
-                 OP " %0, %8, %0 " PAT "\n\t" OP " %1, %9, %1 " PAT "\n\t" OP " %2, %10, %2 " PAT "\n\t"    \
-                 OP " %3, %11, %3 " PAT "\n\t" OP " %4, %12, %4 " PAT "\n\t" OP " %5, %13, %5 " PAT "\n\t"  \
-                 OP " %6, %14, %6 " PAT "\n\t" OP " %7, %15, %7 " PAT                                     \
-                 : "+v"(keep[0]), "+v"(keep[1]), "+v"(keep[2]), "+v"(keep[3]), "+v"(keep[4]), "+v"(keep[5]), \
-                   "+v"(keep[6]), "+v"(keep[7])                                                             \
-                 : "v"(send[0]), "v"(send[1]), "v"(send[2]), "v"(send[3]), "v"(send[4]), "v"(send[5]),     \
-                   "v"(send[6]), "v"(send[7]));                                                             \
-  else if constexpr (K == 4)                                                                                \
-    asm volatile("s_nop 1\n\t"                                                                              \
-                 OP " %0, %4, %0 " PAT "\n\t" OP " %1, %5, %1 " PAT "\n\t" OP " %2, %6, %2 " PAT "\n\t"     \
-                 OP " %3, %7, %3 " PAT                                                                      \
-                 : "+v"(keep[0]), "+v"(keep[1]), "+v"(keep[2]), "+v"(keep[3])                               \
-                 : "v"(send[0]), "v"(send[1]), "v"(send[2]), "v"(send[3]));                                 \
-  else if constexpr (K == 2)                                                                                \
-    asm volatile("s_nop 1\n\t" OP " %0, %2, %0 " PAT "\n\t" OP " %1, %3, %1 " PAT                           \
-                 : "+v"(keep[0]), "+v"(keep[1])                                                             \
-                 : "v"(send[0]), "v"(send[1]));                                                             \
-  else                                                                                                      \
-    asm volatile("s_nop 1\n\t" OP " %0, %1, %0 " PAT : "+v"(keep[0]) : "v"(send[0]))
-  if constexpr (MAX) {
-    if constexpr (PATTERN == 0) S1_OPS("v_max_f32_dpp", "row_ror:8 row_mask:0xf bank_mask:0xf");
-    else if constexpr (PATTERN == 1) S1_OPS("v_max_f32_dpp", "row_half_mirror row_mask:0xf bank_mask:0xf");
-    else if constexpr (PATTERN == 2) S1_OPS("v_max_f32_dpp", "quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf");
-    else S1_OPS("v_max_f32_dpp", "quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf");
-  } else {
-    if constexpr (PATTERN == 0) S1_OPS("v_add_f32_dpp", "row_ror:8 row_mask:0xf bank_mask:0xf");
-    else if constexpr (PATTERN == 1) S1_OPS("v_add_f32_dpp", "row_half_mirror row_mask:0xf bank_mask:0xf");
-    else if constexpr (PATTERN == 2) S1_OPS("v_add_f32_dpp", "quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf");
-    else S1_OPS("v_add_f32_dpp", "quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf");
-  }
-#undef S1_OPS
-}
-template <bool MAX>
-__device__ __forceinline__ float reduce_scatter16(const float (&v)[16], int li) {
-  float keep[8], send[8];
-  const bool h3 = (li & 8) != 0, h2 = (li & 4) != 0, h1 = (li & 2) != 0, h0 = (li & 1) != 0;
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    keep[k] = h3 ? v[8 + k] : v[k];
-    send[k] = h3 ? v[k] : v[8 + k];
-  }
-  s1_rs_step<MAX, 8, 0>(keep, send);
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const float a = keep[k], b = keep[4 + k];
-    keep[k] = h2 ? b : a;
-    send[k] = h2 ? a : b;
-  }
-  s1_rs_step<MAX, 4, 1>(keep, send);
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const float a = keep[k], b = keep[2 + k];
-    keep[k] = h1 ? b : a;
-    send[k] = h1 ? a : b;
-  }
-  s1_rs_step<MAX, 2, 2>(keep, send);
-  {
-    const float a = keep[0], b = keep[1];
-    keep[0] = h0 ? b : a;
-    send[0] = h0 ? a : b;
-  }
-  s1_rs_step<MAX, 1, 3>(keep, send);
-  return keep[0];
-}
-
-// max of three, with no quieting of its operands
-__device__ __forceinline__ float s1_max3(float a, float b, float c) {
-  float r;
-  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-  return r;
-}
 
 // N direct global->LDS copies of 16 bytes per lane under one M0: copy j
 // moves lane i's bytes from g[j] + voff[j] + 1024 j to LDS address lbase +
@@ -1565,17 +1398,25 @@ void launch_s1(const Score1Args& a1, bool full, hipStream_t stream) {
 }  // namespace
 
 ScorePlan plan_score(const Geom& g, int64_t n_units) {
-  (void)n_units;
   ScorePlan sp{};
   const int64_t rows = (int64_t)g.G * g.Wq;
-  sp.single_nt = single_sweep_tiles(g);
-  if (sp.single_nt) {
+  if (resident_fits(g)) {
+    sp.resident = true;
+    sp.rows_wg = resident_rows(g, n_units);
+  } else if ((sp.single_nt = single_sweep_tiles(g)) != 0) {
     sp.rows_wg = S1Use::kRows * kS1BlocksPerSplit;
   } else {
     sp.rows_wg = kScoreWaves * 16 * row_tiles(g);
   }
   sp.n_splits = (int)((rows + sp.rows_wg - 1) / sp.rows_wg);
   return sp;
+}
+
+int64_t max_partial_rows(const Geom& g, int64_t n_units) {
+  const ScorePlan sp = plan_score(g, n_units);
+  const int64_t now = sp.n_splits > 1 ? n_units * sp.n_splits : 0;
+  const int64_t most = std::min(n_units * (((int64_t)g.G * g.Wq + 31) / 32), (int64_t)kSplitMaxWgs);
+  return sp.resident ? std::max(now, most) : now;
 }
 
 hipError_t launch_score(const Geom& g, const ScorePlan& sp, int n_layers, const void* q,
@@ -1597,7 +1438,9 @@ hipError_t launch_score(const Geom& g, const ScorePlan& sp, int n_layers, const 
   if (a.n_blocks == 0) return hipSuccess;
   const int rt = sp.rows_wg / (kScoreWaves * 16);
   hipError_t e;
-  if (sp.single_nt) {
+  if (sp.resident) {
+    e = launch_score_resident(a, sp.rows_wg, stream);
+  } else if (sp.single_nt) {
     Score1Args a1;
     a1.s = a;
     a1.ntw = ((g.N + 15) / 16 + S1Use::kKQ - 1) / S1Use::kKQ;

@@ -49,6 +49,23 @@ def test_version_and_status_strings(lib):
     assert lib.kara_last_hip_error() == b"no HIP error"
 
 
+@pytest.mark.parametrize("over", [
+    dict(), dict(window=256, budget=52), dict(window=701, buffer=33, budget=134, head_dim=64),
+    dict(window=4096, budget=820), dict(window=1280, buffer=32, budget=993, chunk_budget=0, score_queries=32),
+    dict(dtype="f32", head_dim=64, window=700, budget=140), dict(window=96, budget=20),
+])
+def test_workspace_covers_smaller_launches(lib, over):
+    # launches of few units split their rows further: a workspace sized for
+    # more sequences or layers must hold every smaller launch (a server sizes
+    # it once), so the size never falls as units are added
+    p = good_params(**over)
+    sizes = [kara.workspace_size(p, n, layers) for layers in (1, 3) for n in list(range(1, 70)) + [100, 127, 128, 129, 300]]
+    half = len(sizes) // 2
+    for part in (sizes[:half], sizes[half:]):
+        assert all(a <= b for a, b in zip(part, part[1:]))
+    assert all(kara.workspace_size(p, 3 * n, 1) == kara.workspace_size(p, n, 3) for n in (1, 5, 31))
+
+
 def test_workspace_size_scales(lib):
     a = kara.workspace_size(good_params(), 8, 1)
     b = kara.workspace_size(good_params(), 8, 2)

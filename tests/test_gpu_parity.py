@@ -174,6 +174,40 @@ def test_outlier_keys(pos, scale):
         assert (w > 0.25 * case.p["n_q_heads"] // case.p["n_kv_heads"] * case.p["window"]).all()
 
 
+@pytest.mark.parametrize("dtype,d,window,buffer,queries", [
+    ("bf16", 64, 64, 0, 0), ("bf16", 64, 65, 0, 0), ("bf16", 64, 192, 0, 0),       # 4, 8 and 12 tiles, one key part
+    ("bf16", 64, 256, 1, 0), ("bf16", 64, 270, 13, 0),                             # its largest, and the first of two parts
+    ("bf16", 64, 449, 0, 0), ("bf16", 64, 513, 0, 0), ("bf16", 64, 700, 31, 0),    # 16 x 2, 10 x 4 and 12 x 4 tiles
+    ("bf16", 64, 897, 0, 0), ("bf16", 64, 1152, 0, 0), ("bf16", 64, 1153, 0, 0),   # 16 x 4, 18 x 4, and two sweeps past it
+    ("bf16", 128, 1, 0, 0), ("bf16", 128, 512, 0, 17), ("bf16", 128, 513, 0, 0),   # one key; 512 resident, 513 streamed
+    ("f32", 64, 512, 0, 0), ("f32", 64, 513, 0, 0), ("f32", 128, 256, 0, 0), ("f32", 128, 257, 0, 0),
+])
+@pytest.mark.parametrize("outlier", [False, True])
+def test_resident_keys(dtype, d, window, buffer, queries, outlier):
+    # The kernel that keeps a unit's keys in LDS, at the edges of its
+    # instances (key tiles per wave x key parts) and of its range.  With an
+    # outlier, the last key x 256 (exact): its logits pass the first tiles'
+    # maxima by far more than 128 log2 units in a third of the rows, so
+    # their sums overflow and the rows run again from the exact maximum.
+    import kara_check as kc
+    n = window - buffer
+    budget = max(1, n // 5)
+    cfg = ki.workload("batch8", n_seqs=2, n_layers=1, n_q_heads=6, n_kv_heads=2, dtype=dtype, head_dim=d, window=window,
+                      buffer=buffer, budget=budget, chunk_budget=min(4, budget - 1), max_chunk_len=4, prefix=(0, 90),
+                      tail=(0, 9), num_pages=256, key_mode="normal", score_queries=queries)
+    _need_gpu()
+    print(f"\n[case] resident keys {dtype} d={d} N={n} outlier={outlier}", flush=True)
+    case = kc.setup(cfg)
+    if outlier:
+        bs = case.p["block_size"]
+        for s_ in case.geom.trig:
+            j = int(case.geom.win_start[s_]) + n - 1
+            case.kp[0][int(case.geom.block_table[s_, j // bs]), :, j % bs, :] *= 256.0
+        case.host = kc.snapshot(case)
+    rep, _ = kc.full_check(case)
+    print(f"[case] ok {rep}", flush=True)
+
+
 def test_buffer_only_scoring():
     # the ablation without bidirectional attention: only the 64 buffer
     # queries score the 960 compressible keys (q holds those 64 positions)
