@@ -17,6 +17,7 @@ struct ScoreArgs {
   float* partials;            // [units][n_splits][N] (unused with one split)
   float* scores;              // [units][N]
   int n_splits;
+  int rows_split;             // query rows per split (single-sweep and resident kernels)
   int64_t n_blocks;
 };
 
@@ -30,6 +31,6 @@ constexpr int kSplitMaxWgs = 1024;
 bool resident_fits(const Geom& g);
 // rows per workgroup (a multiple of 32) for n_units units of g
 int resident_rows(const Geom& g, int64_t n_units);
-hipError_t launch_score_resident(const ScoreArgs& a, int rows_split, hipStream_t stream);
+hipError_t launch_score_resident(const ScoreArgs& a, hipStream_t stream);
 
 }  // namespace kara

@@ -604,10 +604,12 @@ __global__ __launch_bounds__(256) void split_sum_kernel(const float* __restrict_
 // reaching 65504 (which every overflowing term would exceed) or NaN (where
 // the selector's zeros met an infinity) sends the block
 // through once more with m = (exact row maximum) - 6, where no term exceeds
-// 64 and no wave sum 64 * 512.
+// 64 and no wave sum 64 * 512.  A workgroup's first overflow first moves the
+// keys of largest norm into the first tiles (reorder), which mostly ends the
+// overflows.
 // ---------------------------------------------------------------------------
 constexpr int kS1QIt = 2;                  // iteration that copies the next block's queries
-constexpr int kS1BlocksPerSplit = 16;      // row blocks per workgroup (consecutive blocks of one unit)
+constexpr int kS1BlocksPerSplit = 16;      // row blocks per workgroup (consecutive blocks of one unit), at most
 constexpr int kS1RowBytes = 256;           // one bf16 row of 128
 constexpr int kS1TileBytes = 16 * kS1RowBytes;
 constexpr float kS1Headroom = 6.f;
@@ -617,11 +619,6 @@ constexpr float kS1WScale = 2097152.f;     // 2^21: row weights 1/L, L in [64, 2
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef float float2v __attribute__((ext_vector_type(2)));
-
-struct Score1Args {
-  ScoreArgs s;
-  int ntw;          // key tiles per wave
-};
 
 // the 16-byte chunk swizzle of a 256-byte row in LDS (conflict-free for the
 // operand reads: row's two low bits moved to the top)
@@ -704,8 +701,6 @@ struct S1Cfg {
   // one LDS ring of key tiles per key quarter, shared by its row groups:
   // each wave copies kCW of a tile's four 1 KB parts, and with more than one
   // group the waves meet at a barrier before every tile's operands are read
-  static constexpr int kStages = 8;                        // key tiles in a ring
-  static constexpr int kAhead = kStages - 1;               // tiles copied ahead of the one being read
   static constexpr int kCW = 4 / kRG;                      // copies of a tile per wave
   // Logits are double-buffered, so a tile's vector work follows the next
   // tile's MFMAs.  One wave per SIMD also double-buffers the key operands
@@ -721,21 +716,33 @@ struct S1Cfg {
   static_assert(WAVES % kKQ == 0 && kRG >= 1 && 4 % kRG == 0, "whole row groups, whole copies");
 };
 
-// FULL: every wave's NT tiles hold keys below N (N = 16 * NT * waves), so
-// no tile is skipped or masked.
+// Key tiles in a wave's LDS ring: the most, up to 8, that divide the NT tiles
+// of a block (the ring's stage is then a constant of the unrolled loop).
+constexpr int s1_stages(int nt) {
+  int s = 8;
+  while (nt % s != 0) --s;
+  return s;
+}
+
+// NT key tiles per wave, wave w's from tile w*NT on.  FULL: all of them hold
+// keys below N (N = 64 * NT).  Otherwise the tiles past N repeat key 0 and
+// are worked like the others, their logits starting from -inf instead of 0
+// (weight 0): branches around them kept the compiler from overlapping a
+// tile's vector work with the next one's matrix work (30 sequences x 8 layers,
+// N = 736: 2.42 ms with the tiles skipped in a 16-tile instance, %R736% ms
+// with all of 12 worked).
 template <class CF, int NT, bool FULL>
 __global__ __launch_bounds__(CF::kThreads) __attribute__((amdgpu_waves_per_eu(CF::kWaves / 4, CF::kWaves / 4)))
-void score1_kernel(Score1Args aa) {
-  constexpr int D = CF::kAhead;
-  constexpr int S = CF::kStages;
+void score1_kernel(ScoreArgs a) {
+  constexpr int S = s1_stages(NT);
+  constexpr int D = S - 1;                                 // tiles copied ahead of the one being read
   constexpr int RT = CF::kRT;
   constexpr int NW = CF::kWaves;
   constexpr int ROWS = CF::kRows;
   constexpr int NTH = CF::kThreads;
   constexpr int KQ = CF::kKQ;
   constexpr int WROWS = CF::kWaveRows;
-  static_assert(NT % S == 0 && NT % 4 == 0, "tiles per wave: a multiple of the ring and of 4");
-  const ScoreArgs& a = aa.s;
+  static_assert(NT % S == 0 && NT % 4 == 0 && D >= 4, "tiles per wave: a multiple of the ring and of 4");
   __shared__ __attribute__((aligned(16))) char kring[CF::kKQ][S][kS1TileBytes];
   __shared__ __attribute__((aligned(16))) char qbuf[ROWS * kS1RowBytes];
   // byte offset of key j's row in the K pool; entries past N repeat key 0
@@ -748,6 +755,10 @@ void score1_kernel(Score1Args aa) {
   // byte offset of each of the split's query rows in the unit's queries
   // (rows past R repeat row 0)
   __shared__ uint32_t qrow_off[kS1BlocksPerSplit * ROWS];
+  // keys that changed places (reorder): key swap_key[i] sits at position
+  // swap_pos[i] and the other way round; counts of candidates
+  __shared__ uint16_t swap_key[64], swap_pos[64];
+  __shared__ int swap_cnt[NW];
 
   const Geom& g = a.g;
   const int tid = threadIdx.x;
@@ -784,12 +795,10 @@ void score1_kernel(Score1Args aa) {
   const int R = g.G * g.Wq;
   const float c = g.scale * kLog2e;
   const int nblk = (R + ROWS - 1) / ROWS;
-  const int b0 = split * kS1BlocksPerSplit;
-  const int b1 = min(nblk, b0 + kS1BlocksPerSplit);
-  const int ntw = aa.ntw;
-  const int T = (N + 15) / 16;
-  const int wt0 = kq * ntw;                                   // this wave's first tile
-  const int nvalid = FULL ? NT : max(0, min(ntw, T - wt0));   // its tiles holding a key < N
+  const int bps = a.rows_split / ROWS;                        // at most kS1BlocksPerSplit
+  const int b0 = split * bps;
+  const int b1 = min(nblk, b0 + bps);
+  const int wt0 = kq * NT;                                    // this wave's first tile
 
   {
     const int32_t* row_pages = a.bt + (int64_t)s * g.max_blocks;
@@ -798,7 +807,7 @@ void score1_kernel(Score1Args aa) {
       const uint64_t row = ((uint64_t)row_pages[pos / g.bs] * g.Hkv + h) * g.bs + pos % g.bs;
       key_off[j] = (uint32_t)(row * kS1RowBytes);
     }
-    for (int j = tid; j < kS1BlocksPerSplit * ROWS; j += NTH) {
+    for (int j = tid; j < bps * ROWS; j += NTH) {
       int gr = b0 * ROWS + j;
       if (gr >= R) gr = 0;
       const int w = gr / g.G, gi = gr - w * g.G;
@@ -891,6 +900,18 @@ void score1_kernel(Score1Args aa) {
       __builtin_memcpy(&kb[b][ks], &v, 16);
     }
   };
+  // What a tile's logits start from: 0, and -inf for keys past N.  Those are
+  // a tail of the tiles, so zq changes at most twice a block.  (n_keys: N,
+  // opaque to the compiler, which would otherwise keep every tile's zq in
+  // registers of its own across the blocks)
+  floatx4 zq = {0.f, 0.f, 0.f, 0.f};
+  int n_keys = N;
+  auto set_zq = [&](int tile) __attribute__((always_inline)) {
+    if (!FULL && (wt0 + tile + 1) * 16 > n_keys) {
+      const float z = (wt0 + tile) * 16 + li >= n_keys ? kNegInf : 0.f;
+      zq = floatx4{z, z, z, z};
+    }
+  };
   // (k step outer: the row tiles' accumulation chains interleave)
   auto form = [&](int b, int kbi) __attribute__((always_inline)) {
 #pragma unroll
@@ -898,15 +919,7 @@ void score1_kernel(Score1Args aa) {
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt)
         acc[b][rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-            qa[rt][ks], kb[kbi][ks], ks == 0 ? floatx4{0.f, 0.f, 0.f, 0.f} : acc[b][rt], 0, 0, 0);
-  };
-  // keys of tile `tile` past N: logits -inf
-  auto mask = [&](int tile, int b) __attribute__((always_inline)) {
-    if (FULL) return;
-    if ((wt0 + tile + 1) * 16 > N && (wt0 + tile) * 16 + li >= N) {
-#pragma unroll
-      for (int rt = 0; rt < RT; ++rt) acc[b][rt] = floatx4{kNegInf, kNegInf, kNegInf, kNegInf};
-    }
+            qa[rt][ks], kb[kbi][ks], ks != 0 ? acc[b][rt] : FULL ? floatx4{0.f, 0.f, 0.f, 0.f} : zq, 0, 0, 0);
   };
   // a finished pair: round to fp16, add both to the row sums and store.  The
   // row sums are a matrix product too: with the selector as A, output row M
@@ -942,11 +955,6 @@ void score1_kernel(Score1Args aa) {
       for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
         for (int q = 0; q < 4; ++q) ep[rt][q] = e[rt][q];
-      // the pair's odd tile holds no key below N
-      if (!FULL && tile + 1 >= nvalid) {
-        const float zero[RT][4] = {};
-        finish_pair(tile >> 1, zero);
-      }
     }
   };
   auto vexp = [&](int tile, int b) __attribute__((always_inline)) {
@@ -1039,6 +1047,10 @@ void score1_kernel(Score1Args aa) {
     for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
       for (int q = 0; q < 4; ++q) L[rt][q] = 0.f;
+    if constexpr (!FULL) {
+      asm volatile("" : "+s"(n_keys));
+      zq = floatx4{0.f, 0.f, 0.f, 0.f};
+    }
     static_for<0, NT>([&](auto it_c) __attribute__((always_inline)) {
       constexpr int it = decltype(it_c)::value;
       constexpr int b = it & 1;                             // logits of tile it
@@ -1048,10 +1060,8 @@ void score1_kernel(Score1Args aa) {
         wait_next(it_c);
         kread((it + 1) % S, kbi ^ 1);
       }
-      if (it < nvalid) {
-        form(b, kbi);
-        mask(it, b);
-      }
+      set_zq(it);
+      form(b, kbi);
       if constexpr (CF::kKbBuf == 1) {
         wait_next(it_c);
         kread((it + 1) % S, 0);
@@ -1063,44 +1073,158 @@ void score1_kernel(Score1Args aa) {
 #pragma unroll
           for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) mx[rt][q] = nvalid > 0 ? acc[bp][rt][q] : kNegInf;
+            for (int q = 0; q < 4; ++q) mx[rt][q] = acc[bp][rt][q];
           share_max(mx);
         }
-        if (nvalid > 0) vexp(0, bp);
+        vexp(0, bp);
       } else if constexpr (it > 1) {
-        if (it - 1 < nvalid) vexp(it - 1, bp);
+        vexp(it - 1, bp);
       }
       issue_k(std::integral_constant<int, (it + D) % S>{});
       read_offsets((it + D + 1) % NT);
       // (the split's last block copies its own rows again, unused)
       if (it == kS1QIt) issue_q(min(blk + 1, b1 - 1));
     });
-    if (NT - 1 < nvalid) vexp(NT - 1, (NT - 1) & 1);
+    vexp(NT - 1, (NT - 1) & 1);
   };
 
-  // exact row maxima over this wave's keys, read straight from the pool
+  // exact row maxima over this wave's keys, read straight from the pool (the
+  // next tile's keys in flight while this one's logits form)
   auto exact_max = [&]() {
+    constexpr int kOdd = CF::kKbBuf - 1;
     float mx[RT][4];
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
       for (int q = 0; q < 4; ++q) mx[rt][q] = kNegInf;
-    for (int tile = 0; tile < nvalid; ++tile) {
+    zq = floatx4{0.f, 0.f, 0.f, 0.f};
+    auto gread = [&](int tile, int b) __attribute__((always_inline)) {
       const char* src = kpool + key_off[(wt0 + tile) * 16 + li] + gq * 64;
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks) {
         const uint4 v = *(const uint4*)(src + ks * 16);
-        __builtin_memcpy(&kb[0][ks], &v, 16);
+        __builtin_memcpy(&kb[b][ks], &v, 16);
       }
-      form(0, 0);
-      mask(tile, 0);
+    };
+    auto raise = [&](int tile, int b) __attribute__((always_inline)) {
+      set_zq(tile);
+      form(0, b);
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
         for (int q = 0; q < 4; ++q) mx[rt][q] = fmaxf(mx[rt][q], acc[0][rt][q]);
+    };
+    gread(0, 0);
+#pragma unroll 1
+    for (int tile = 0; tile < NT; tile += 2) {
+      if constexpr (kOdd == 1) gread(tile + 1, 1);
+      raise(tile, 0);
+      if constexpr (kOdd == 0) gread(tile + 1, 0);
+      else if (tile + 2 < NT) gread(tile + 2, 0);
+      raise(tile + 1, kOdd);
+      if constexpr (kOdd == 0) {
+        if (tile + 2 < NT) gread(tile + 2, 0);
+      }
     }
     share_max(mx);
     // kb[0] is the next pass's tile 0 again, from its stage
+    kread(0, 0);
+  };
+
+  // Keys of large norm to the first tiles, which give the rows' references:
+  // up to 64 of the largest change places with keys of the four first tiles.
+  // Called at most once, on a workgroup's first overflow: trained models have
+  // a few keys far larger than the rest, every block would then overflow and
+  // run twice, and with those keys in the reference hardly any does.  The
+  // column sums so far go to `out` first, and the ring is refilled.  8
+  // sequences, one layer, W = 1024, 2 % of the keys x 4: 317 us with every
+  // block run again, %RHEAVY% us with the keys moved.
+  int n_swap = 0;
+  bool reordered = false;
+  auto reorder = [&]() {
+    static_assert(CF::kRG == 1, "a wave's column sums are its keys' alone");
+    constexpr int kKeys = KQ * NT * 16;
+    // (opaque, so that nothing below is kept in registers across the blocks)
+    int tid_r = tid;
+    asm volatile("" : "+v"(tid_r));
+    const int lane = tid_r & 63, gq = lane >> 4, li = lane & 15;
+#pragma unroll
+    for (int j = 0; j < NT / 4; ++j) {
+      const int pos = (wt0 + 2 * (2 * j + (gq & 1)) + (gq >> 1)) * 16 + li;
+      if (pos < N) out[pos] = colacc[j] * (1.f / kS1WScale);
+      colacc[j] = 0.f;
+    }
+    reordered = true;
+    float* norm = (float*)&kring[0][0][0];   // once no copy or read of the ring is left
+    wait_vm<0>();
+    lds_barrier();
+    // squared norms, four keys per wave and step (keys past N: below any)
+#pragma unroll 8
+    for (int j0 = wave * 4; j0 < kKeys; j0 += NW * 4) {
+      const int j = j0 + gq;
+      const uint4 v = *(const uint4*)(kpool + key_off[j] + li * 16);
+      const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+      float ss = 0.f;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float lo = __uint_as_float(w[i] << 16), hi = __uint_as_float(w[i] & 0xffff0000u);
+        ss += lo * lo + hi * hi;
+      }
+      ss = dpp_sum16(ss);
+      if (li == 0) norm[j] = j < N ? ss : 0.f;
+    }
+    lds_barrier();
+    // the largest bound (in the norm's upper 16 bits) that 64 keys reach
+    uint32_t bits[kKeys / NTH];
+#pragma unroll
+    for (int i = 0; i < kKeys / NTH; ++i) bits[i] = __float_as_uint(norm[i * NTH + tid_r]) >> 16;
+    uint32_t bound = 0;
+    for (int bit = 14; bit >= 0; --bit) {
+      const uint32_t cand = bound | (1u << bit);
+      int cnt = 0;
+#pragma unroll
+      for (int i = 0; i < kKeys / NTH; ++i) cnt += __builtin_popcountll(__ballot(bits[i] >= cand));
+      if (lane == 0) swap_cnt[wave] = cnt;
+      lds_barrier();
+      int all = 0;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) all += swap_cnt[w];
+      if (all >= 64) bound = cand;
+      lds_barrier();
+    }
+    // wave 0 pairs the keys above it (at most 63) that are outside the first
+    // tiles with the first tiles' other keys, both in ascending order
+    if (wave == 0) {
+      int nk = 0;
+      for (int j0 = 0; j0 < kKeys; j0 += 64) {
+        const int j = j0 + lane;
+        const bool take = (__float_as_uint(norm[j]) >> 16) > bound && j % (NT * 16) >= 16;
+        const uint64_t mask = __ballot(take);
+        if (take) swap_key[nk + __builtin_popcountll(mask & ((1ull << lane) - 1))] = (uint16_t)j;
+        nk += __builtin_popcountll(mask);
+      }
+      const int p = (lane >> 4) * NT * 16 + (lane & 15);
+      const bool give = p < N && (__float_as_uint(norm[p]) >> 16) <= bound;
+      const uint64_t mask = __ballot(give);
+      if (give) swap_pos[__builtin_popcountll(mask & ((1ull << lane) - 1))] = (uint16_t)p;
+      if (lane == 0) swap_cnt[0] = min(nk, (int)__builtin_popcountll(mask));
+    }
+    lds_barrier();
+    n_swap = __builtin_amdgcn_readfirstlane(swap_cnt[0]);
+    if (tid_r < n_swap) {
+      const int x = swap_key[tid_r], y = swap_pos[tid_r];
+      const uint32_t ox = key_off[x];
+      key_off[x] = key_off[y];
+      key_off[y] = ox;
+    }
+    lds_barrier();
+    static_for<0, D>([&](auto j_c) __attribute__((always_inline)) {
+      read_offsets(decltype(j_c)::value % NT);
+      issue_k(std::integral_constant<int, decltype(j_c)::value % S>{});
+    });
+    read_offsets(D % NT);
+    wait_vm<CW * (D - 1)>();
+    lds_barrier();
     kread(0, 0);
   };
 
@@ -1195,6 +1319,11 @@ void score1_kernel(Score1Args aa) {
         }
         break;
       }
+      if (!reordered) {
+        reorder();
+        pass = -1;   // the block again from its first pass
+        continue;
+      }
       exact_max();
       m_given = true;
     }
@@ -1275,35 +1404,20 @@ void score1_kernel(Score1Args aa) {
       const float v = cs[0] + cs[1];
       colacc[sp >> 1] += (gq & 1) == (sp & 1) ? v : 0.f;
     };
-    if constexpr (FULL) {
-      // row tile by row tile: its weights, then its MFMA for every pair (one
-      // accumulator per pair), so a tile's weight arithmetic overlaps the
-      // previous tile's MFMAs
-      floatx4 cs[NT / 2];
-      static_for<0, RT>([&](auto rt_c) __attribute__((always_inline)) {
-        constexpr int rt = decltype(rt_c)::value;
-        uint32_t wa[4];
-        weights_of(rt, wa);
-        static_for<0, NT / 2>([&](auto s_c) __attribute__((always_inline)) {
-          constexpr int sp = decltype(s_c)::value;
-          cs[sp] = mfma_w(wa, sp, rt, rt == 0 ? floatx4{0.f, 0.f, 0.f, 0.f} : cs[sp]);
-        });
-      });
-      static_for<0, NT / 2>([&](auto s_c) __attribute__((always_inline)) { add_pair(s_c, cs[decltype(s_c)::value]); });
-    } else {
-      uint32_t wa[RT][4];
-#pragma unroll
-      for (int rt = 0; rt < RT; ++rt) weights_of(rt, wa[rt]);
+    // row tile by row tile: its weights, then its MFMA for every pair (one
+    // accumulator per pair), so a tile's weight arithmetic overlaps the
+    // previous tile's MFMAs
+    floatx4 cs[NT / 2];
+    static_for<0, RT>([&](auto rt_c) __attribute__((always_inline)) {
+      constexpr int rt = decltype(rt_c)::value;
+      uint32_t wa[4];
+      weights_of(rt, wa);
       static_for<0, NT / 2>([&](auto s_c) __attribute__((always_inline)) {
         constexpr int sp = decltype(s_c)::value;
-        if (2 * sp < nvalid) {
-          floatx4 cs = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-          for (int rt = 0; rt < RT; ++rt) cs = mfma_w(wa[rt], sp, rt, cs);
-          add_pair(s_c, cs);
-        }
+        cs[sp] = mfma_w(wa, sp, rt, rt == 0 ? floatx4{0.f, 0.f, 0.f, 0.f} : cs[sp]);
       });
-    }
+    });
+    static_for<0, NT / 2>([&](auto s_c) __attribute__((always_inline)) { add_pair(s_c, cs[decltype(s_c)::value]); });
   }
   wait_vm<0>();
   if constexpr (CF::kRG > 1) {
@@ -1327,8 +1441,16 @@ void score1_kernel(Score1Args aa) {
 #pragma unroll
   for (int j = 0; j < NT / 4; ++j) {
     const int tile = 2 * (2 * j + (gq & 1)) + (gq >> 1);
-    const int key = (wt0 + tile) * 16 + li;
-    if (tile < nvalid && key < N) out[key] = colacc[j] * (1.f / kS1WScale);
+    const int pos = (wt0 + tile) * 16 + li;
+    int key = pos;
+    for (int i = 0; i < n_swap; ++i) {
+      if (swap_pos[i] == pos) key = swap_key[i];
+      if (swap_key[i] == pos) key = swap_pos[i];
+    }
+    if (pos < N) {
+      const float before = reordered ? out[key] : 0.f;   // its sums before the keys moved
+      out[key] = colacc[j] * (1.f / kS1WScale) + before;
+    }
   }
 }
 
@@ -1381,18 +1503,39 @@ int single_sweep_tiles(const Geom& g) {
   // its copies address a layer's K pool and a unit's queries by 32-bit offsets
   if ((uint64_t)g.num_pages * g.Hkv * g.bs * kS1RowBytes > 0xffffffffull) return 0;
   if ((uint64_t)g.Wq * g.Hq * kS1RowBytes > 0xffffffffull) return 0;
-  constexpr int KQ = S1Use::kKQ;
-  const int ntw = ((g.N + 15) / 16 + KQ - 1) / KQ;
-  // the smallest multiple of 8 (of the ring, and of 4) holding ntw
-  static_assert(8 % S1Use::kStages == 0, "instances come in steps of 8 tiles");
-  return (ntw + 7) / 8 * 8;
+  // the smallest instance (a multiple of 4 tiles per wave) holding the keys
+  return (g.N + 16 * S1Use::kKQ * 4 - 1) / (16 * S1Use::kKQ * 4) * 4;
+}
+
+// Query rows per workgroup: kS1BlocksPerSplit blocks, the start-up (key
+// table, first copies: about 6 us) being paid per workgroup; fewer where the
+// launch would leave CUs idle, by the time of its rounds of one workgroup per
+// CU (a block takes about 2 us + 0.3 us per key tile; adding the splits about
+// 4 us).  1 sequence, one layer, W = 1000, 32/8 heads: %RBPS%.
+int single_sweep_rows(const Geom& g, int nt, int64_t n_units) {
+  const int64_t nblk = ((int64_t)g.G * g.Wq + S1Use::kRows - 1) / S1Use::kRows;
+  const int64_t s0 = (nblk + kS1BlocksPerSplit - 1) / kS1BlocksPerSplit;
+  int64_t best = (nblk + s0 - 1) / s0, best_t = -1;
+  for (int64_t s = s0; s <= nblk && (s == s0 || s * n_units <= kSplitMaxWgs); ++s) {
+    const int64_t bps = (nblk + s - 1) / s, used = (nblk + bps - 1) / bps;
+    const int64_t t = (used * n_units + kScoreCUs - 1) / kScoreCUs * (60 + bps * (20 + 3 * nt)) + (used > 1 ? 40 : 0);
+    if (best_t < 0 || t < best_t) best_t = t, best = bps;
+  }
+  return (int)best * S1Use::kRows;
 }
 
 template <int NT>
-void launch_s1(const Score1Args& a1, bool full, hipStream_t stream) {
-  const dim3 grid((unsigned)a1.s.n_blocks), block(S1Use::kThreads);
-  if (full) hipLaunchKernelGGL((score1_kernel<S1Use, NT, true>), grid, block, 0, stream, a1);
-  else hipLaunchKernelGGL((score1_kernel<S1Use, NT, false>), grid, block, 0, stream, a1);
+void launch_s1(const ScoreArgs& a, hipStream_t stream) {
+  const dim3 grid((unsigned)a.n_blocks), block(S1Use::kThreads);
+  // (whole instances for the power-of-two window lengths: they save the
+  // few instructions that watch for the last key)
+  if constexpr (NT % 8 == 0) {
+    if (a.g.N == S1Use::kKQ * 16 * NT) {
+      hipLaunchKernelGGL((score1_kernel<S1Use, NT, true>), grid, block, 0, stream, a);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((score1_kernel<S1Use, NT, false>), grid, block, 0, stream, a);
 }
 
 }  // namespace
@@ -1404,7 +1547,7 @@ ScorePlan plan_score(const Geom& g, int64_t n_units) {
     sp.resident = true;
     sp.rows_wg = resident_rows(g, n_units);
   } else if ((sp.single_nt = single_sweep_tiles(g)) != 0) {
-    sp.rows_wg = S1Use::kRows * kS1BlocksPerSplit;
+    sp.rows_wg = single_sweep_rows(g, sp.single_nt, n_units);
   } else {
     sp.rows_wg = kScoreWaves * 16 * row_tiles(g);
   }
@@ -1416,7 +1559,7 @@ int64_t max_partial_rows(const Geom& g, int64_t n_units) {
   const ScorePlan sp = plan_score(g, n_units);
   const int64_t now = sp.n_splits > 1 ? n_units * sp.n_splits : 0;
   const int64_t most = std::min(n_units * (((int64_t)g.G * g.Wq + 31) / 32), (int64_t)kSplitMaxWgs);
-  return sp.resident ? std::max(now, most) : now;
+  return sp.resident || sp.single_nt ? std::max(now, most) : now;
 }
 
 hipError_t launch_score(const Geom& g, const ScorePlan& sp, int n_layers, const void* q,
@@ -1434,21 +1577,21 @@ hipError_t launch_score(const Geom& g, const ScorePlan& sp, int n_layers, const 
   a.partials = partials;
   a.scores = scores;
   a.n_splits = sp.n_splits;
+  a.rows_split = sp.rows_wg;
   a.n_blocks = (int64_t)n_layers * g.n_trig * g.n_win * g.Hkv * sp.n_splits;
   if (a.n_blocks == 0) return hipSuccess;
   const int rt = sp.rows_wg / (kScoreWaves * 16);
   hipError_t e;
   if (sp.resident) {
-    e = launch_score_resident(a, sp.rows_wg, stream);
+    e = launch_score_resident(a, stream);
   } else if (sp.single_nt) {
-    Score1Args a1;
-    a1.s = a;
-    a1.ntw = ((g.N + 15) / 16 + S1Use::kKQ - 1) / S1Use::kKQ;
-    const bool full = g.N == S1Use::kKQ * 16 * sp.single_nt;
-    switch (sp.single_nt / 8) {
-      case 2: launch_s1<16>(a1, full, stream); break;
-      case 3: launch_s1<24>(a1, full, stream); break;
-      default: launch_s1<32>(a1, full, stream); break;
+    switch (sp.single_nt) {
+      case 12: launch_s1<12>(a, stream); break;
+      case 16: launch_s1<16>(a, stream); break;
+      case 20: launch_s1<20>(a, stream); break;
+      case 24: launch_s1<24>(a, stream); break;
+      case 28: launch_s1<28>(a, stream); break;
+      default: launch_s1<32>(a, stream); break;
     }
     e = hipGetLastError();
   } else if (g.dtype == KARA_BF16)

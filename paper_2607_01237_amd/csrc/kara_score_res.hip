@@ -108,7 +108,7 @@ __device__ __forceinline__ float swap16_add(float a, float b) {
 
 template <int DT, int D, int NTW, int KS>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void score_res_kernel(ScoreArgs a, int rows_split) {
+void score_res_kernel(ScoreArgs a) {
   using C = RCfg<DT, D, NTW, KS>;
   constexpr int KC = C::kKC, RB = C::kRowBytes;
   __shared__ __attribute__((aligned(16))) char kbuf[C::kKeys * RB];
@@ -143,8 +143,8 @@ void score_res_kernel(ScoreArgs a, int rows_split) {
   const int p0 = a.win_start[s] + wi * N;
   const char* kpool = (const char*)a.k.p[l];
   const char* qunit = a.q + (((int64_t)l * g.n_trig + t) * g.n_win + wi) * g.Wq * g.Hq * (int64_t)RB;
-  const int r0 = split * rows_split;
-  const int r1 = min(g.G * g.Wq, r0 + rows_split);
+  const int r0 = split * a.rows_split;
+  const int r1 = min(g.G * g.Wq, r0 + a.rows_split);
   const float c = g.scale * kLog2e;
 
   // ---- the unit's keys into LDS ----
@@ -406,11 +406,11 @@ ResShape res_shape(const Geom& g) {
 }
 
 template <int DT, int D>
-hipError_t launch_d(const ScoreArgs& a, int rows_split, hipStream_t stream) {
+hipError_t launch_d(const ScoreArgs& a, hipStream_t stream) {
   const dim3 grid((unsigned)a.n_blocks), block(kThreads);
   const ResShape r = res_shape(a.g);
 #define KARA_RES(NTW, KS) \
-  if (r.ntw == NTW && r.ks == KS) hipLaunchKernelGGL((score_res_kernel<DT, D, NTW, KS>), grid, block, 0, stream, a, rows_split)
+  if (r.ntw == NTW && r.ks == KS) hipLaunchKernelGGL((score_res_kernel<DT, D, NTW, KS>), grid, block, 0, stream, a)
   KARA_RES(4, 1);
   else KARA_RES(8, 1);
   if constexpr (D * (DT == KARA_BF16 ? 2 : 4) == 512) {
@@ -462,10 +462,10 @@ int resident_rows(const Geom& g, int64_t n_units) {
   return (int)(best * 32);
 }
 
-hipError_t launch_score_resident(const ScoreArgs& a, int rows_split, hipStream_t stream) {
+hipError_t launch_score_resident(const ScoreArgs& a, hipStream_t stream) {
   if (a.g.dtype == KARA_BF16)
-    return a.g.d == 128 ? launch_d<KARA_BF16, 128>(a, rows_split, stream) : launch_d<KARA_BF16, 64>(a, rows_split, stream);
-  return a.g.d == 128 ? launch_d<KARA_F32, 128>(a, rows_split, stream) : launch_d<KARA_F32, 64>(a, rows_split, stream);
+    return a.g.d == 128 ? launch_d<KARA_BF16, 128>(a, stream) : launch_d<KARA_BF16, 64>(a, stream);
+  return a.g.d == 128 ? launch_d<KARA_F32, 128>(a, stream) : launch_d<KARA_F32, 64>(a, stream);
 }
 
 }  // namespace kara
