@@ -579,7 +579,7 @@ __global__ __launch_bounds__(256) void split_sum_kernel(const float* __restrict_
 //
 // Every logit is formed and exponentiated once.  A workgroup of 4 waves, one
 // per SIMD, takes a unit's query rows 64 at a time (a row block); within a
-// block wave w owns the keys of tiles [w*ntw, (w+1)*ntw) (16 keys a tile)
+// block wave w owns the keys of tiles [w*NT, (w+1)*NT) (16 keys a tile)
 // against all 64 rows, so its tiles' weights e = 2^(x - m) fit in its
 // accumulation registers as fp16 (64 rows x 512 keys = 256 registers).  The
 // reference m of a row is shared by the four waves: the maximum of their
@@ -604,12 +604,13 @@ __global__ __launch_bounds__(256) void split_sum_kernel(const float* __restrict_
 // reaching 65504 (which every overflowing term would exceed) or NaN (where
 // the selector's zeros met an infinity) sends the block
 // through once more with m = (exact row maximum) - 6, where no term exceeds
-// 64 and no wave sum 64 * 512.  A workgroup's first overflow first moves the
-// keys of largest norm into the first tiles (reorder), which mostly ends the
-// overflows.
+// 64 and no wave sum 64 * 512.  An overflow in a workgroup's first blocks first
+// moves the keys of largest norm into the first tiles (reorder), which mostly
+// ends the overflows.
 // ---------------------------------------------------------------------------
 constexpr int kS1QIt = 2;                  // iteration that copies the next block's queries
 constexpr int kS1BlocksPerSplit = 16;      // row blocks per workgroup (consecutive blocks of one unit), at most
+constexpr int kS1ReorderBlocks = 6;        // an overflow this early in a workgroup moves the large keys
 constexpr int kS1RowBytes = 256;           // one bf16 row of 128
 constexpr int kS1TileBytes = 16 * kS1RowBytes;
 constexpr float kS1Headroom = 6.f;
@@ -729,7 +730,7 @@ constexpr int s1_stages(int nt) {
 // are worked like the others, their logits starting from -inf instead of 0
 // (weight 0): branches around them kept the compiler from overlapping a
 // tile's vector work with the next one's matrix work (30 sequences x 8 layers,
-// N = 736: 2.42 ms with the tiles skipped in a 16-tile instance, %R736% ms
+// N = 736: 2.21 ms with the tiles skipped in a 16-tile instance, 1.84 ms
 // with all of 12 worked).
 template <class CF, int NT, bool FULL>
 __global__ __launch_bounds__(CF::kThreads) __attribute__((amdgpu_waves_per_eu(CF::kWaves / 4, CF::kWaves / 4)))
@@ -1133,12 +1134,15 @@ void score1_kernel(ScoreArgs a) {
 
   // Keys of large norm to the first tiles, which give the rows' references:
   // up to 64 of the largest change places with keys of the four first tiles.
-  // Called at most once, on a workgroup's first overflow: trained models have
-  // a few keys far larger than the rest, every block would then overflow and
-  // run twice, and with those keys in the reference hardly any does.  The
-  // column sums so far go to `out` first, and the ring is refilled.  8
-  // sequences, one layer, W = 1024, 2 % of the keys x 4: 317 us with every
-  // block run again, %RHEAVY% us with the keys moved.
+  // Called at most once, on an overflow in a workgroup's first blocks: trained
+  // models have a few keys far larger than the rest, every block would then
+  // overflow and run twice, and with those keys in the reference hardly any
+  // does.  (It takes about three blocks' time, so a workgroup that overflows
+  // late, and thus seldom, runs that block again instead: with 1 % of the
+  // blocks overflowing, scoring took 0.8 % longer when any overflow moved the
+  // keys.)  The column sums so far go to `out` first, and the ring is
+  // refilled.  8 sequences, one layer, W = 1024, 2 % of the keys x 4: 315 us
+  // with every block run again, 152 us with the keys moved.
   int n_swap = 0;
   bool reordered = false;
   auto reorder = [&]() {
@@ -1319,7 +1323,7 @@ void score1_kernel(ScoreArgs a) {
         }
         break;
       }
-      if (!reordered) {
+      if (!reordered && blk - b0 < kS1ReorderBlocks) {
         reorder();
         pass = -1;   // the block again from its first pass
         continue;
@@ -1511,7 +1515,8 @@ int single_sweep_tiles(const Geom& g) {
 // table, first copies: about 6 us) being paid per workgroup; fewer where the
 // launch would leave CUs idle, by the time of its rounds of one workgroup per
 // CU (a block takes about 2 us + 0.3 us per key tile; adding the splits about
-// 4 us).  1 sequence, one layer, W = 1000, 32/8 heads: %RBPS%.
+// 4 us).  1 sequence, one layer, W = 1000, 32/8 heads: 116 us in workgroups of
+// 16 blocks, 27 us in ones of 2.
 int single_sweep_rows(const Geom& g, int nt, int64_t n_units) {
   const int64_t nblk = ((int64_t)g.G * g.Wq + S1Use::kRows - 1) / S1Use::kRows;
   const int64_t s0 = (nblk + kS1BlocksPerSplit - 1) / kS1BlocksPerSplit;
@@ -1565,7 +1570,7 @@ int64_t max_partial_rows(const Geom& g, int64_t n_units) {
 hipError_t launch_score(const Geom& g, const ScorePlan& sp, int n_layers, const void* q,
                         const PoolPtrs& k_pools, const int32_t* trig, const int32_t* block_table,
                         const int32_t* win_start, const int32_t* status, float* partials,
-                        float* scores, hipStream_t stream) {
+                        float* scores, bool sum, hipStream_t stream) {
   ScoreArgs a;
   a.g = g;
   a.q = (const char*)q;
@@ -1598,7 +1603,7 @@ hipError_t launch_score(const Geom& g, const ScorePlan& sp, int n_layers, const 
     e = g.d == 128 ? launch_d<KARA_BF16, 128>(a, rt, stream) : launch_d<KARA_BF16, 64>(a, rt, stream);
   else
     e = g.d == 128 ? launch_d<KARA_F32, 128>(a, rt, stream) : launch_d<KARA_F32, 64>(a, rt, stream);
-  if (e != hipSuccess || sp.n_splits == 1) return e;
+  if (e != hipSuccess || sp.n_splits == 1 || !sum) return e;
   const int64_t units = a.n_blocks / sp.n_splits;
   hipLaunchKernelGGL(split_sum_kernel, dim3((unsigned)units, (unsigned)((g.N + 255) / 256)), dim3(256), 0, stream,
                      partials, scores, g.N, sp.n_splits);
