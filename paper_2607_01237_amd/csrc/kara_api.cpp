@@ -133,13 +133,13 @@ hipError_t for_layer_chunks(int n_layers, const void* const* k_pools, const void
 hipError_t run_score(const Geom& g, const ScorePlan& sp, int n_layers, const void* q,
                      const void* const* k_pools, const int32_t* trig, const int32_t* bt,
                      const int32_t* win_start, const int32_t* status, float* partials,
-                     float* scores, hipStream_t stream) {
+                     float* scores, bool sum, hipStream_t stream) {
   const int64_t q_layer = (int64_t)g.n_trig * g.n_win * g.Wq * g.Hq * g.d * g.esize;
   const int64_t units_layer = (int64_t)g.n_trig * g.n_win * g.Hkv;
   return for_layer_chunks(n_layers, k_pools, nullptr, [&](int l0, int cnt, const PoolPtrs& kp, const PoolPtrs&) {
     return launch_score(g, sp, cnt, (const char*)q + l0 * q_layer, kp, trig, bt, win_start, status,
                         partials + l0 * units_layer * sp.n_splits * g.N, scores + l0 * units_layer * g.N,
-                        stream);
+                        sum, stream);
   });
 }
 
@@ -197,9 +197,10 @@ kara_status_t compress(const kara_params_t* p, int32_t n_trig, const int32_t* tr
   hipError_t e = launch_validate(g, trig, block_table, seq_lens, win_start, status, false, s);
   if (e == hipSuccess)
     e = run_score(g, sp, n_layers, q, (const void* const*)k_pools, trig, block_table, win_start, status,
-                  partials, scores_buf, s);
+                  partials, scores_buf, false, s);
   if (e == hipSuccess)
-    e = launch_select(g, units, kSelectDiscrete | kSelectKept, scores_buf, nullptr, discrete, kept_buf, s);
+    e = launch_select(g, units, kSelectDiscrete | kSelectKept, scores_buf, partials, sp.n_splits, scores, nullptr,
+                      discrete, kept_buf, s);
   if (e == hipSuccess)
     e = run_compact(g, n_layers, trig, kept_buf, k_pools, v_pools, block_table, seq_lens, win_start,
                     status, s);
@@ -284,7 +285,7 @@ kara_status_t kara_score_window(const kara_params_t* p, int32_t n_trig, const in
   hipError_t e = launch_validate(g, trig, block_table, seq_lens, win_start, status, false, s);
   if (e == hipSuccess)
     e = run_score(g, sp, n_layers, q, k_pools, trig, block_table, win_start, status, (float*)(ws + wl.partials),
-                  scores, s);
+                  scores, true, s);
   return hip_status(e);
 }
 
@@ -296,7 +297,7 @@ kara_status_t kara_select(const kara_params_t* p, int64_t n_units, const float* 
   if (n_units < 0 || n_units > INT32_MAX) return KARA_ERR_INVALID_ARG;
   if (n_units == 0) return KARA_OK;
   if (!scores || !discrete) return KARA_ERR_INVALID_ARG;
-  return hip_status(launch_select(g, n_units, kSelectDiscrete, scores, nullptr, discrete, nullptr,
+  return hip_status(launch_select(g, n_units, kSelectDiscrete, scores, nullptr, 1, nullptr, nullptr, discrete, nullptr,
                                   (hipStream_t)stream));
 }
 
@@ -308,7 +309,7 @@ kara_status_t kara_token2chunk(const kara_params_t* p, int64_t n_units, const fl
   if (n_units < 0 || n_units > INT32_MAX) return KARA_ERR_INVALID_ARG;
   if (n_units == 0) return KARA_OK;
   if (!scores || !discrete || !kept) return KARA_ERR_INVALID_ARG;
-  return hip_status(launch_select(g, n_units, kSelectKept, scores, discrete, nullptr, kept,
+  return hip_status(launch_select(g, n_units, kSelectKept, scores, nullptr, 1, nullptr, discrete, nullptr, kept,
                                   (hipStream_t)stream));
 }
 
@@ -320,7 +321,7 @@ kara_status_t kara_select_kept(const kara_params_t* p, int64_t n_units, const fl
   if (n_units < 0 || n_units > INT32_MAX) return KARA_ERR_INVALID_ARG;
   if (n_units == 0) return KARA_OK;
   if (!scores || !discrete || !kept) return KARA_ERR_INVALID_ARG;
-  return hip_status(launch_select(g, n_units, kSelectDiscrete | kSelectKept, scores, nullptr, discrete, kept,
+  return hip_status(launch_select(g, n_units, kSelectDiscrete | kSelectKept, scores, nullptr, 1, nullptr, nullptr, discrete, kept,
                                   (hipStream_t)stream));
 }
 

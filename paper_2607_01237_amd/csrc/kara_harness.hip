@@ -2,6 +2,7 @@
 // append into the paged cache, and split-key decode attention of one query
 // per (layer, sequence, query head) over the compressed cache.  Not part of
 // the compression step; same paged layout.
+#include <algorithm>
 #include <cmath>
 #include <type_traits>
 
@@ -21,67 +22,125 @@ constexpr int kDecWgTarget = 4096;   // workgroups a launch keeps when its split
 
 // ---------------------------------------------------------------- append
 
-__global__ void append_check_kernel(Geom g, int n, const int32_t* __restrict__ seqs, int n_new,
-                                    const int32_t* __restrict__ bt, const int32_t* __restrict__ seq_lens,
-                                    int32_t* __restrict__ status) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= n) return;
+constexpr int kAppendThreads = 256;
+constexpr int kAppendUnroll = 8;       // 16-byte pieces per thread
+// Appends of up to this many tokens check their sequence in the copying
+// workgroups and in the committing one: a launch less (8 sequences, one token:
+// a decoding step 43 -> 39 us of host time).  Longer ones have a table row to
+// read per check and keep it in a kernel of its own.
+constexpr int kAppendFusedTokens = 32;
+
+// Status of listed sequence j, by all threads of a workgroup; the same value
+// in each.
+__device__ int append_status(const Geom& g, int n, const int32_t* __restrict__ seqs, int n_new,
+                             const int32_t* __restrict__ bt, const int32_t* __restrict__ seq_lens, int j) {
   const int s = seqs[j];
-  if (s < 0 || s >= g.n_seqs) {
-    status[j] = KARA_SEQ_BAD_INDEX;
-    return;
-  }
-  int st = 0;
-  for (int o = 0; o < n; ++o)
-    if (o != j && seqs[o] == s) st |= KARA_SEQ_DUP_TRIGGER;
+  if (s < 0 || s >= g.n_seqs) return KARA_SEQ_BAD_INDEX;
+  int dup = 0;
+  for (int o = threadIdx.x; o < n; o += kAppendThreads) dup |= o != j && seqs[o] == s;
   const int64_t len = seq_lens[s];
   const int64_t new_len = len + n_new;
-  if (len < 0 || new_len > (int64_t)g.max_blocks * g.bs) {
-    status[j] = st | KARA_SEQ_BAD_WINDOW;
-    return;
-  }
-  const int32_t* row = bt + (int64_t)s * g.max_blocks;
-  for (int64_t b = len / g.bs; b < (new_len + g.bs - 1) / g.bs; ++b) {
-    const int pg = row[b];
-    if (pg < 0 || pg >= g.num_pages) {
-      st |= KARA_SEQ_BAD_PAGE;
-      break;
+  const bool fits = len >= 0 && new_len <= (int64_t)g.max_blocks * g.bs;
+  int bad = 0;
+  if (fits) {
+    const int32_t* row = bt + (int64_t)s * g.max_blocks;
+    for (int b = (int)(len / g.bs) + threadIdx.x; b < (int)((new_len + g.bs - 1) / g.bs); b += kAppendThreads) {
+      const int pg = row[b];
+      bad |= pg < 0 || pg >= g.num_pages;
     }
   }
-  status[j] = st;
+  const int any = __syncthreads_or(dup | (bad << 1));
+  // (the two flags come back as one "any": told apart by a second vote only
+  // when something is wrong)
+  if (!any) return fits ? KARA_SEQ_OK : KARA_SEQ_BAD_WINDOW;
+  const int d = __syncthreads_or(dup) ? KARA_SEQ_DUP_TRIGGER : 0;
+  const int p = __syncthreads_or(bad) ? KARA_SEQ_BAD_PAGE : 0;
+  return d | p | (fits ? 0 : KARA_SEQ_BAD_WINDOW);
 }
 
-// One thread per 16 bytes of new rows: grid (chunks of n * n_new * Hkv rows, layer, K|V).
-__global__ __launch_bounds__(256) void append_kernel(Geom g, int n, const int32_t* __restrict__ seqs, int n_new,
-                                                     const char* __restrict__ k_new, const char* __restrict__ v_new,
-                                                     PoolPtrs kp, PoolPtrs vp, const int32_t* __restrict__ bt,
-                                                     const int32_t* __restrict__ seq_lens,
-                                                     const int32_t* __restrict__ status) {
+__global__ __launch_bounds__(kAppendThreads) void append_check_kernel(Geom g, int n, const int32_t* __restrict__ seqs,
+                                                                      int n_new, const int32_t* __restrict__ bt,
+                                                                      const int32_t* __restrict__ seq_lens,
+                                                                      int32_t* __restrict__ status) {
+  const int st = append_status(g, n, seqs, n_new, bt, seq_lens, blockIdx.x);
+  if (threadIdx.x == 0) status[blockIdx.x] = st;
+}
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+// One workgroup per `toks` tokens of a listed sequence: grid (sequences x token
+// chunks, layer, K|V), kAppendUnroll pieces of 16 bytes per thread, all loaded
+// before the first is stored.  The new rows are read once (nontemporal); the
+// pool rows are stored to stay cached, as scoring reads the keys next (stored
+// nontemporally, the append of 4 x 4 layers of 16,893 tokens gained 30 us and
+// the scoring after it lost 95 us).  128 sequences x 4 layers of 1,280 tokens
+// (5.4 GB): 1093 us with one piece per thread, 1006 us so.
+template <bool CHECK>
+__global__ __launch_bounds__(kAppendThreads) void append_kernel(Geom g, int n, const int32_t* __restrict__ seqs, int n_new,
+                                                                int toks, int chunks, const char* __restrict__ k_new,
+                                                                const char* __restrict__ v_new, PoolPtrs kp, PoolPtrs vp,
+                                                                const int32_t* __restrict__ bt,
+                                                                const int32_t* __restrict__ seq_lens,
+                                                                const int32_t* __restrict__ status) {
+  const int j = blockIdx.x / chunks;
+  const int tok0 = (blockIdx.x - j * chunks) * toks;
   const int l = blockIdx.y;
   const int kv = blockIdx.z;
+  if constexpr (CHECK) {
+    if (append_status(g, n, seqs, n_new, bt, seq_lens, j) != KARA_SEQ_OK) return;
+  } else {
+    if (status[j] != 0) return;
+  }
+  const int s = seqs[j];
   const int row_bytes = g.d * g.esize;
   const int cpr = row_bytes / 16;
-  const int64_t per_layer = (int64_t)n * n_new * g.Hkv * cpr;   // 16-byte pieces of one layer
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= per_layer) return;
-  const int c = (int)(i % cpr);
-  const int64_t row = i / cpr;                 // [n][n_new][Hkv]
-  const int h = (int)(row % g.Hkv);
-  const int tok = (int)((row / g.Hkv) % n_new);
-  const int j = (int)(row / ((int64_t)g.Hkv * n_new));
-  if (status[j] != 0) return;
-  const int s = seqs[j];
-  const int pos = seq_lens[s] + tok;
-  const int64_t page = bt[(int64_t)s * g.max_blocks + pos / g.bs];
-  const char* src = (kv ? v_new : k_new) + ((int64_t)l * per_layer + i) * 16;
-  char* dst = (char*)(kv ? vp.p[l] : kp.p[l]) + ((page * g.Hkv + h) * g.bs + pos % g.bs) * (int64_t)row_bytes + c * 16;
-  *(uint4*)dst = *(const uint4*)src;
+  const int per_tok = g.Hkv * cpr;              // pieces of one token
+  const int count = min(toks, n_new - tok0) * per_tok;
+  const int pos0 = seq_lens[s] + tok0;
+  const int32_t* row_pages = bt + (int64_t)s * g.max_blocks;
+  const char* src = (kv ? v_new : k_new) + (((int64_t)l * n + j) * n_new + tok0) * per_tok * 16;
+  char* pool = (char*)(kv ? vp.p[l] : kp.p[l]);
+  for (int i0 = threadIdx.x; i0 < count; i0 += kAppendThreads * kAppendUnroll) {
+    u32x4 v[kAppendUnroll];
+    int64_t dst[kAppendUnroll];
+#pragma unroll
+    for (int k = 0; k < kAppendUnroll; ++k) {
+      const int i = i0 + k * kAppendThreads;
+      if (i < count) {
+        v[k] = __builtin_nontemporal_load((const u32x4*)(src + (int64_t)i * 16));
+        const int tok = i / per_tok, x = i - tok * per_tok;
+        const int h = x / cpr, c = x - h * cpr;
+        const int pos = pos0 + tok, b = pos / g.bs;
+        dst[k] = (((int64_t)row_pages[b] * g.Hkv + h) * g.bs + (pos - b * g.bs)) * row_bytes + c * 16;
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < kAppendUnroll; ++k)
+      if (i0 + k * kAppendThreads < count) *(u32x4*)(pool + dst[k]) = v[k];
+  }
 }
 
-__global__ void append_commit_kernel(int n, const int32_t* __restrict__ seqs, int n_new,
-                                     int32_t* __restrict__ seq_lens, const int32_t* __restrict__ status) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j < n && status[j] == 0) seq_lens[seqs[j]] += n_new;
+// CHECK: a workgroup per listed sequence, which finds and writes its status
+// and waits for every thread to have read the length; else a thread each.
+// (Distinct sequences: a duplicate is flagged and its length left alone, so no
+// workgroup's check sees another's new length.)
+template <bool CHECK>
+__global__ __launch_bounds__(kAppendThreads) void append_commit_kernel(Geom g, int n, const int32_t* __restrict__ seqs,
+                                                                       int n_new, const int32_t* __restrict__ bt,
+                                                                       int32_t* __restrict__ seq_lens,
+                                                                       int32_t* __restrict__ status) {
+  if constexpr (CHECK) {
+    const int j = blockIdx.x;
+    const int st = append_status(g, n, seqs, n_new, bt, seq_lens, j);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      status[j] = st;
+      if (st == KARA_SEQ_OK) seq_lens[seqs[j]] += n_new;
+    }
+  } else {
+    const int j = blockIdx.x * blockDim.x + threadIdx.x;
+    if (j < n && status[j] == 0) seq_lens[seqs[j]] += n_new;
+  }
 }
 
 // ---------------------------------------------------------------- decode
@@ -506,22 +565,35 @@ kara_status_t kara_harness_kv_append(const kara_params_t* p, int32_t n, const in
       !pools_ok((const void* const*)k_pools, n_layers) || !pools_ok((const void* const*)v_pools, n_layers))
     return KARA_ERR_INVALID_ARG;
   hipStream_t s = (hipStream_t)stream;
-  hipLaunchKernelGGL(append_check_kernel, dim3((n + 255) / 256), dim3(256), 0, s, g, n, seqs, n_new, block_table,
-                     seq_lens, status);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return hip_status(e);
   PoolPtrs kp{}, vp{};
   for (int i = 0; i < n_layers; ++i) {
     kp.p[i] = k_pools[i];
     vp.p[i] = v_pools[i];
   }
-  const int64_t pieces = (int64_t)n * n_new * g.Hkv * (g.d * g.esize / 16);
-  hipLaunchKernelGGL(append_kernel, dim3((unsigned)((pieces + 255) / 256), (unsigned)n_layers, 2), dim3(256), 0, s,
-                     g, n, seqs, n_new, (const char*)k_new, (const char*)v_new, kp, vp, block_table, seq_lens,
+  // tokens per workgroup: enough pieces for its threads' loads in flight
+  const int per_tok = g.Hkv * (g.d * g.esize / 16);
+  const int toks = std::min(n_new, std::max(1, 2 * kAppendThreads * kAppendUnroll / per_tok));
+  const int64_t chunks = ((int64_t)n_new + toks - 1) / toks;
+  const dim3 copy_grid((unsigned)(n * chunks), (unsigned)n_layers, 2), block(kAppendThreads);
+  if (n_new <= kAppendFusedTokens) {
+    hipLaunchKernelGGL((append_kernel<true>), copy_grid, block, 0, s, g, n, seqs, n_new, toks, (int)chunks,
+                       (const char*)k_new, (const char*)v_new, kp, vp, block_table, seq_lens, status);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return hip_status(e);
+    hipLaunchKernelGGL((append_commit_kernel<true>), dim3((unsigned)n), block, 0, s, g, n, seqs, n_new, block_table,
+                       seq_lens, status);
+    return hip_status(hipGetLastError());
+  }
+  hipLaunchKernelGGL(append_check_kernel, dim3((unsigned)n), block, 0, s, g, n, seqs, n_new, block_table, seq_lens,
                      status);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return hip_status(e);
+  hipLaunchKernelGGL((append_kernel<false>), copy_grid, block, 0, s, g, n, seqs, n_new, toks, (int)chunks,
+                     (const char*)k_new, (const char*)v_new, kp, vp, block_table, seq_lens, status);
   e = hipGetLastError();
   if (e != hipSuccess) return hip_status(e);
-  hipLaunchKernelGGL(append_commit_kernel, dim3((n + 255) / 256), dim3(256), 0, s, n, seqs, n_new, seq_lens, status);
+  hipLaunchKernelGGL((append_commit_kernel<false>), dim3((n + kAppendThreads - 1) / kAppendThreads), block, 0, s, g, n,
+                     seqs, n_new, block_table, seq_lens, status);
   return hip_status(hipGetLastError());
 }
 

@@ -60,16 +60,19 @@ ScorePlan plan_score(const Geom& g, int64_t n_units);
 // writes.  Launches of few units split their rows further, so this is what a
 // workspace sized for n_units must hold for a smaller launch to fit it too.
 int64_t max_partial_rows(const Geom& g, int64_t n_units);
+// (sum: false leaves the partials of more than one split to launch_select)
 hipError_t launch_score(const Geom& g, const ScorePlan& sp, int n_layers, const void* q,
                         const PoolPtrs& k_pools, const int32_t* trig, const int32_t* block_table,
                         const int32_t* win_start, const int32_t* status, float* partials,
-                        float* scores, hipStream_t stream);
+                        float* scores, bool sum, hipStream_t stream);
 
 // Selection (kara_select.hip).  mode bit 1: discrete top-k; bit 2: Token2Chunk
-// + fill (from discrete_in when bit 1 is clear).
+// + fill (from discrete_in when bit 1 is clear).  n_splits > 1: the scores are
+// the sums of the units' partial rows in split order, written to scores_out
+// unless that is null; else they are read from scores.
 enum { kSelectDiscrete = 1, kSelectKept = 2 };
-hipError_t launch_select(const Geom& g, int64_t n_units, int mode, const float* scores,
-                         const int32_t* discrete_in, int32_t* discrete_out, int32_t* kept_out,
+hipError_t launch_select(const Geom& g, int64_t n_units, int mode, const float* scores, const float* partials,
+                         int n_splits, float* scores_out, const int32_t* discrete_in, int32_t* discrete_out, int32_t* kept_out,
                          hipStream_t stream);
 
 // Compaction and metadata (kara_pages.hip).

@@ -311,8 +311,9 @@ __device__ void select_top(const KeyT (&key)[EPT], const bool (&elig)[EPT], bool
 
 template <int EPT>
 __global__ __launch_bounds__(kSelThreads) void select_kernel(
-    Geom g, int mode, const float* __restrict__ scores, const int32_t* __restrict__ disc_in,
-    int32_t* __restrict__ disc_out, int32_t* __restrict__ kept_out) {
+    Geom g, int mode, const float* __restrict__ scores, const float* __restrict__ partials, int n_splits,
+    float* __restrict__ scores_out, const int32_t* __restrict__ disc_in, int32_t* __restrict__ disc_out,
+    int32_t* __restrict__ kept_out) {
   extern __shared__ __attribute__((aligned(16))) char sel_lds[];
   const int N = g.N;
   SelSmem sm;
@@ -326,9 +327,23 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
   const int tid = threadIdx.x;
   const int k = g.k_disc;
 
-  for (int j = tid; j < N; j += kSelThreads) {
-    sm.a[j] = scores[u * N + j];
-    sm.mark[j] = 0;
+  // (a unit's scores, or the sum of its row splits' partial column sums: a
+  // launch and a pass over the scores less than summing them first)
+  if (n_splits > 1) {
+    const float* src = partials + u * n_splits * (int64_t)N;
+    for (int j = tid; j < N; j += kSelThreads) {
+      float v = src[j];
+#pragma unroll 8
+      for (int p = 1; p < n_splits; ++p) v += src[(int64_t)p * N + j];
+      sm.a[j] = v;
+      sm.mark[j] = 0;
+      if (scores_out) scores_out[u * N + j] = v;
+    }
+  } else {
+    for (int j = tid; j < N; j += kSelThreads) {
+      sm.a[j] = scores[u * N + j];
+      sm.mark[j] = 0;
+    }
   }
   __syncthreads();
 
@@ -450,16 +465,17 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
 
 }  // namespace
 
-hipError_t launch_select(const Geom& g, int64_t n_units, int mode, const float* scores,
-                         const int32_t* discrete_in, int32_t* discrete_out, int32_t* kept_out,
+hipError_t launch_select(const Geom& g, int64_t n_units, int mode, const float* scores, const float* partials,
+                         int n_splits, float* scores_out, const int32_t* discrete_in, int32_t* discrete_out, int32_t* kept_out,
                          hipStream_t stream) {
   if (n_units <= 0) return hipSuccess;
   if (g.N <= 8 * kSelThreads)
     hipLaunchKernelGGL(select_kernel<8>, dim3((unsigned)n_units), dim3(kSelThreads), sel_lds_bytes(g.N, g.k_disc), stream,
-                       g, mode, scores, discrete_in, discrete_out, kept_out);
+                       g, mode, scores, partials, n_splits, scores_out, discrete_in, discrete_out, kept_out);
   else
     hipLaunchKernelGGL(select_kernel<kSelEptMax>, dim3((unsigned)n_units), dim3(kSelThreads),
-                       sel_lds_bytes(g.N, g.k_disc), stream, g, mode, scores, discrete_in, discrete_out, kept_out);
+                       sel_lds_bytes(g.N, g.k_disc), stream, g, mode, scores, partials, n_splits, scores_out,
+                       discrete_in, discrete_out, kept_out);
   return hipGetLastError();
 }
 

@@ -200,3 +200,53 @@ def test_kv_append(dtype, d):
         assert np.array_equal(ki.raw_numpy(kpd[l]).view(np.uint8), want_k[l].view(np.uint8)), f"K pool {l}"
         assert np.array_equal(ki.raw_numpy(vpd[l]).view(np.uint8), want_v[l].view(np.uint8)), f"V pool {l}"
     print("[case] ok", flush=True)
+
+
+@pytest.mark.parametrize("n_new", [1, 16, 32, 33])
+@pytest.mark.parametrize("dtype,Hkv,d,bs", [("bf16", 8, 128, 16), ("f32", 3, 64, 7)])
+def test_kv_append_lengths(n_new, dtype, Hkv, d, bs):
+    # both forms of the append (the check inside the copying and committing
+    # workgroups up to 32 tokens, a kernel of its own above), every status
+    # bit and its combinations; unflagged rows land bit for bit, nothing
+    # else changes
+    from paper_2607_01237_amd import kara
+    _need_gpu()
+    dev = torch.device("cuda:0")
+    rng = np.random.default_rng(n_new)
+    L, max_blocks = 2, -(-(100 + 40) // bs)
+    cap = max_blocks * bs
+    lens = np.array([0, bs - 1, bs, 60, 50, 40, 3, cap - n_new, cap - n_new + 1, 44], dtype=np.int32)
+    p, table, _ = _geom(rng, len(lens), Hkv, Hkv, d, dtype, bs, np.minimum(lens + n_new, cap), max_blocks)
+    table[5, (40 + n_new - 1) // bs] = p["num_pages"]        # past the pool
+    table[9, 44 // bs] = -1
+    seqs = np.array([3, 0, 5, 12, 1, 6, 6, 7, 2, 4, 8, 9, 9, -1], dtype=np.int32)
+    dup, page, window, index = kara.SEQ_DUP_TRIGGER, kara.SEQ_BAD_PAGE, kara.SEQ_BAD_WINDOW, kara.SEQ_BAD_INDEX
+    want = np.array([0, 0, page, index, 0, dup, dup, 0, 0, 0, window, dup | page, dup | page, index], dtype=np.int32)
+    print(f"\n[case] append {dtype} d={d} n_new={n_new}", flush=True)
+    params = kara.make_params(p, len(lens))
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator(device=dev).manual_seed(3)
+    R = lambda *shape: torch.randn(shape, generator=g, device=dev).to(dt)  # noqa: E731
+    n = len(seqs)
+    kp, vp = ([R(p["num_pages"], Hkv, bs, d) for _ in range(L)] for _ in range(2))
+    k0, v0 = [t.clone() for t in kp], [t.clone() for t in vp]
+    k_new, v_new = R(L, n, n_new, Hkv, d), R(L, n, n_new, Hkv, d)
+    T = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(dev)  # noqa: E731
+    sl, st = T(lens), torch.full((n,), -7, dtype=torch.int32, device=dev)
+    kara.kv_append(params, T(seqs), k_new, v_new, kp, vp, T(table), sl, st)
+    torch.cuda.synchronize()
+    assert np.array_equal(st.cpu().numpy(), want), st
+    want_lens = lens.copy()
+    for j, s in enumerate(seqs):
+        if want[j]:
+            continue
+        pos = lens[s] + np.arange(n_new)
+        pg, slot = T(table[s, pos // bs].astype(np.int64)), T((pos % bs).astype(np.int64))
+        for l in range(L):
+            k0[l][pg, :, slot] = k_new[l, j]
+            v0[l][pg, :, slot] = v_new[l, j]
+        want_lens[s] += n_new
+    assert np.array_equal(sl.cpu().numpy(), want_lens)
+    for l in range(L):
+        assert torch.equal(kp[l], k0[l]) and torch.equal(vp[l], v0[l]), f"pools of layer {l}"
+    print("[case] ok", flush=True)

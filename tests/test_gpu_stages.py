@@ -208,3 +208,45 @@ def test_page_mapped_twice_is_flagged():
     rep, gpu = kc.full_check(case)
     assert gpu["status"][1] == oracle.SEQ_DUP_PAGE and gpu["status"][0] == 0 and gpu["status"][2] == 0
     print("dup page", rep)
+
+
+@pytest.mark.parametrize("num_pages,max_blocks", [(4096, 300), (262144, 300), (262145, 300), (300000, 9000)])
+def test_validation_of_page_tables(num_pages, max_blocks):
+    # the duplicate-page check's three forms (a bitmap of the pool, up to
+    # 262,144 pages; the row in LDS; the row in memory past 8,192 blocks):
+    # which blocks count, and pages outside the pool
+    from paper_2607_01237_amd import kara
+    _need_gpu()
+    print(f"\n[case] validate {num_pages} pages, {max_blocks} blocks", flush=True)
+    bs, n = 16, 8
+    nb = max_blocks - 2
+    rng = np.random.default_rng(5)
+    table = np.full((n, max_blocks), -1, dtype=np.int32)
+    for s in range(n):
+        table[s, :nb] = rng.permutation(num_pages)[:nb]
+    table[:, nb - 1] = num_pages - 1 - np.arange(n)          # the pool's last pages, not elsewhere in the row
+    for s in range(n):
+        row = table[s, :nb - 1]
+        clash = row >= num_pages - n
+        row[clash] = np.setdiff1d(np.arange(num_pages - n), row)[:int(clash.sum())]
+    b0 = nb - 70                                             # first block of the window
+    want = np.zeros(n, dtype=np.int32)
+    table[1, b0 + 3] = table[1, b0 + 40]                     # twice among the blocks written
+    table[2, b0 + 3] = table[2, 7]                           # once there, once before
+    table[3, 5] = table[3, 7]                                # both before: not checked
+    table[4, b0 + 1] = -1
+    table[5, nb - 1] = num_pages
+    table[6, 2] = -5                                         # before the window: not checked
+    table[7, b0] = table[7, nb - 1]
+    table[7, b0 + 9] = num_pages + 7
+    want[[1, 2]] = kara.SEQ_DUP_PAGE
+    want[[4, 5]] = kara.SEQ_BAD_PAGE
+    want[7] = kara.SEQ_DUP_PAGE | kara.SEQ_BAD_PAGE
+    p = dict(window=1024, buffer=0, budget=205, chunk_budget=16, max_chunk_len=8, head_dim=128, n_q_heads=8, n_kv_heads=1,
+             block_size=bs, num_pages=num_pages, max_blocks_per_seq=max_blocks, dtype="bf16", scale=0.0)
+    st = torch.full((n,), -7, dtype=torch.int32, device="cuda")
+    kara.validate(kara.make_params(p, n), _dev(np.arange(n, dtype=np.int32)), _dev(table),
+                  _dev(np.full(n, nb * bs, dtype=np.int32)), _dev(np.full(n, b0 * bs, dtype=np.int32)), st)
+    torch.cuda.synchronize()
+    assert np.array_equal(st.cpu().numpy(), want), st
+    print("[case] ok", flush=True)
