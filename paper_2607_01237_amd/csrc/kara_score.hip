@@ -1458,25 +1458,30 @@ void score1_kernel(ScoreArgs a) {
   }
 }
 
-// Row tiles per wave.  At most four (512 rows per workgroup), two for fp32
-// with 128-wide heads, whose operands take twice the registers.  Fewer when
-// a unit has few query rows (scoring by a buffer or an observation window):
-// the count that pads the unit's rows least, the larger one on a tie, since
-// each workgroup streams all of the unit's keys.
-int row_tiles(const Geom& g) {
+// Row tiles per wave of the two-sweep kernel.  At most four (512 rows per
+// workgroup), two for fp32 with 128-wide heads, whose operands take twice the
+// registers.  A workgroup streams all of the unit's keys whatever its rows: it
+// takes about rt + 0.8 units of time for 128 * rt rows in bf16 (a whole launch
+// of 256 sequence-heads, d = 64, N = 1024, 2048 rows each: 1425, 1097, 1137 and
+// 979 us with 1 to 4 tiles), rt + 0.2 in fp32, which is bound by the matrix
+// instructions.  So: the least of workgroups times that, the larger count on
+// a tie; and where a launch stays within kSplitMaxWgs workgroups, another count
+// if its rounds of one workgroup per CU take less.
+// (Choosing the count that pads least took 1402 rows in 11 workgroups of one
+// tile, 704 us, instead of 3 of four, 500 us.)
+int row_tiles(const Geom& g, int64_t n_units) {
   const int max_rt = (g.dtype == KARA_F32 && g.d == 128) ? 2 : 4;
   const int64_t rows = (int64_t)g.G * g.Wq;
+  auto wgs = [&](int rt) { return (rows + kScoreWaves * 16 * rt - 1) / (kScoreWaves * 16 * rt); };
+  auto one = [&](int rt) { return 10 * rt + (g.dtype == KARA_BF16 ? 8 : 2); };
   int best = max_rt;
-  int64_t best_pad = -1;
-  for (int rt = max_rt; rt >= 1; --rt) {
-    const int64_t per = (int64_t)kScoreWaves * 16 * rt;
-    const int64_t pad = (rows + per - 1) / per * per - rows;
-    if (best_pad < 0 || pad < best_pad) {
-      best = rt;
-      best_pad = pad;
-    }
-  }
-  return best;
+  for (int rt = max_rt - 1; rt >= 1; --rt)
+    if (wgs(rt) * one(rt) < wgs(best) * one(best)) best = rt;
+  auto rounds = [&](int rt) { return (n_units * wgs(rt) + kScoreCUs - 1) / kScoreCUs * one(rt); };
+  int small = best;
+  for (int rt = max_rt; rt >= 1; --rt)
+    if (n_units * wgs(rt) <= kSplitMaxWgs && rounds(rt) < rounds(small)) small = rt;
+  return small;
 }
 
 template <int DT, int D>
@@ -1554,17 +1559,20 @@ ScorePlan plan_score(const Geom& g, int64_t n_units) {
   } else if ((sp.single_nt = single_sweep_tiles(g)) != 0) {
     sp.rows_wg = single_sweep_rows(g, sp.single_nt, n_units);
   } else {
-    sp.rows_wg = kScoreWaves * 16 * row_tiles(g);
+    sp.rows_wg = kScoreWaves * 16 * row_tiles(g, n_units);
   }
   sp.n_splits = (int)((rows + sp.rows_wg - 1) / sp.rows_wg);
   return sp;
 }
 
 int64_t max_partial_rows(const Geom& g, int64_t n_units) {
-  const ScorePlan sp = plan_score(g, n_units);
-  const int64_t now = sp.n_splits > 1 ? n_units * sp.n_splits : 0;
-  const int64_t most = std::min(n_units * (((int64_t)g.G * g.Wq + 31) / 32), (int64_t)kSplitMaxWgs);
-  return sp.resident || sp.single_nt ? std::max(now, most) : now;
+  // (a plan splits further than the one for many units only within
+  // kSplitMaxWgs workgroups)
+  const int64_t rows = (int64_t)g.G * g.Wq;
+  const ScorePlan sp = plan_score(g, std::max<int64_t>(n_units, kSplitMaxWgs + 1));
+  const int64_t least = sp.resident ? 32 : sp.single_nt ? S1Use::kRows : kScoreWaves * 16;
+  const int64_t far = n_units * ((rows + least - 1) / least);
+  return std::max(sp.n_splits > 1 ? n_units * sp.n_splits : 0, std::min(far, (int64_t)kSplitMaxWgs));
 }
 
 hipError_t launch_score(const Geom& g, const ScorePlan& sp, int n_layers, const void* q,

@@ -450,12 +450,15 @@ int resident_rows(const Geom& g, int64_t n_units) {
   // each its start (the key copies and column sums, about `fixed`) and its
   // iterations, in units of about 0.27 us (measured at d = 64).  Split only
   // while the launch stays within kSplitMaxWgs.
-  const int64_t per_it = g.dtype == KARA_BF16 ? 2 + r.ntw : 2 + r.ntw * (g.d / 16), fixed = 20, sum_launch = 15;
+  const int64_t per_it = g.dtype == KARA_BF16 ? 2 + r.ntw : 2 + r.ntw * (g.d / 16), fixed = 20, sum_launch = 5;
   int64_t best = chunks, best_t = -1;
   for (int64_t s = 1; s <= chunks && (s == 1 || s * n_units <= kSplitMaxWgs); ++s) {
     const int64_t c = (chunks + s - 1) / s;
     const int64_t used = (chunks + c - 1) / c;
-    const int64_t t = (used * n_units + kScoreCUs - 1) / kScoreCUs * (fixed + (c + rg - 1) / rg * per_it) +
+    // (a step's time is that of two waves on a SIMD; of one, half)
+    const int64_t waves = (c < rg ? c : rg) * r.ks;
+    const int64_t step = waves > 4 ? per_it : (per_it + 1) / 2;
+    const int64_t t = (used * n_units + kScoreCUs - 1) / kScoreCUs * (fixed + (c + rg - 1) / rg * step) +
                       (used > 1 ? sum_launch : 0);
     if (best_t < 0 || t < best_t) best_t = t, best = c;
   }
