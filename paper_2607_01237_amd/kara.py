@@ -209,7 +209,7 @@ def _ptr(t):
         raise KaraError("marshal", ERR_INVALID_ARG, "tensor is not on the GPU")
     if not t.is_contiguous():
         raise KaraError("marshal", ERR_INVALID_ARG, "tensor is not contiguous")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 # ---- host-side shape checks: the library takes bare pointers and cannot
@@ -247,8 +247,10 @@ def _tables(p, block_table, seq_lens, win_start=None):
 
 
 def _pools(p, pools, name):
+    n, dt = p.num_pages * p.n_kv_heads * p.block_size * p.head_dim, _dt(p)
     for i, t in enumerate(pools):
-        _need(f"{name}[{i}]", t, p.num_pages * p.n_kv_heads * p.block_size * p.head_dim, _dt(p))
+        if t is None or t.dtype != dt or t.numel() < n:
+            _need(f"{name}[{i}]", t, n, dt)
 
 
 def _units(p, n_layers, n_trig, n_windows=1):
@@ -262,16 +264,16 @@ def _step_outputs(p, units, scores, discrete, kept):
 
 
 def _ptr_array(tensors):
-    arr = (ctypes.c_void_p * len(tensors))()
-    for i, t in enumerate(tensors):
-        arr[i] = _ptr(t).value
-    return arr
+    return (ctypes.c_void_p * len(tensors))(*[_ptr(t) for t in tensors])
 
 
 def _stream(stream):
+    if stream is not None:
+        return stream.cuda_stream
+    # (the handle alone: torch.cuda.current_stream() builds a Stream object on
+    # the way, about 4 us a call)
     import torch
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def abi_version() -> int:
@@ -492,7 +494,7 @@ def recompute_queries(p, m: KaraModel, trig, weights, hidden_in, hidden_out, k_p
             _need(f"weights[{i}].{f}", w[f], size, _dt(p))
     arr = (LayerWeights * n)()
     for i, w in enumerate(weights):
-        arr[i] = LayerWeights(*[_ptr(w[f]).value for f, _ in LayerWeights._fields_])
+        arr[i] = LayerWeights(*[_ptr(w[f]) for f, _ in LayerWeights._fields_])
     _check("kara_recompute_queries", load().kara_recompute_queries(
         ctypes.byref(p), ctypes.byref(m), trig.numel(), _ptr(trig), n, arr, _ptr(hidden_in), _ptr(hidden_out),
         _ptr_array(k_pools), _ptr_array(v_pools), _ptr(block_table), _ptr(seq_lens), _ptr(win_start),
