@@ -154,9 +154,10 @@ template <int DT, int D, int GP>
 struct DCfg {
   static constexpr int kES = DT == KARA_BF16 ? 2 : 4;
   static constexpr int kRowBytes = D * kES;
-  // 16-key tiles per block, and buffers of its keys: what fits the registers
-  // of two waves per SIMD
-  static constexpr int kTB = DT == KARA_BF16 && (GP < 16 || D == 64) ? 2 : 1;
+  // 16-key tiles per block, and buffers of its keys: a block of 16 rows of 256
+  // bytes or more leaves registers for a third wave per SIMD (G <= 5), 4 % on
+  // launches of a few workgroups per CU against 32; half as long rows take 32.
+  static constexpr int kTB = DT == KARA_BF16 && D == 64 ? 2 : 1;
   static constexpr int kKBuf = DT == KARA_F32 && D == 128 && GP == 16 ? 1 : 2;
   static constexpr int kBlock = 16 * kTB;                  // keys per block
   static constexpr int kKC = kRowBytes / 64;               // 16-byte chunks of a key row per lane
@@ -196,9 +197,9 @@ __device__ __forceinline__ float swap16_add(float a, float b) {
 //
 // Bound by the K and V bytes.  The rows' pool offsets are formed once per
 // split into LDS, so no load waits on the block table, and the waves take
-// the split's 32-key blocks (16 in fp32) in turn, each with the next block's
-// keys and this block's values in flight while it works: about 20 KB per
-// wave.  S^T = K Q^T on the matrix cores puts query li of lane (gq, li)
+// the split's 16-key blocks (32 for bf16 at d = 64) in turn, each with the
+// next block's keys and this block's values in flight while it works: 8 to 12
+// KB per wave.  S^T = K Q^T on the matrix cores puts query li of lane (gq, li)
 // against keys 16t + 4gq + r, and the value rows are loaded so that row gq of
 // the wave holds exactly those keys: a weight reaches the 16 lanes that hold
 // its key's columns by one DPP row broadcast, and P V runs in fp32 on the
