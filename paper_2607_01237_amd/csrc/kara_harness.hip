@@ -328,6 +328,11 @@ __global__ __launch_bounds__(kDecThreads, 2) void decode_split_kernel(
       }
       sv[t] = acc;
     }
+    // Wait states between the last product and the first read of its result:
+    // the branch below comes between, and past it the compiler gave 1 where 8
+    // (bf16) or 10 (fp32) are needed, so with three waves per SIMD the maximum
+    // read what the registers held before.  12 cycles per block.
+    asm volatile("s_nop 7\n\ts_nop 3" : "+v"(sv[TB - 1]));
     const int left = nk - blk * C::kBlock;
     if (left < C::kBlock) {
 #pragma unroll

@@ -149,6 +149,44 @@ def test_decode_splits(dtype, Hq, Hkv, d, n, L, bs, max_len):
     print("[case] ok", flush=True)
 
 
+@pytest.mark.parametrize("dtype,Hq,Hkv,d,max_len", [
+    ("bf16", 40, 8, 128, 2100),   # 4096 units: 1024-key splits of 16-key blocks, three of them
+    ("f32", 32, 8, 64, 2100),
+    ("bf16", 32, 2, 128, 8300),   # G = 16; 1024 units, nine 1024-key splits
+])
+def test_decode_full_chip(dtype, Hq, Hkv, d, max_len):
+    # enough workgroups for every wave slot: the waits inside the kernel must
+    # not depend on how many waves a SIMD holds.  Bound as above.
+    from paper_2607_01237_amd import kara
+    _need_gpu()
+    dev = torch.device("cuda:0")
+    n, L, bs = 128, 4, 16
+    rng = np.random.default_rng(d + Hq)
+    lens = rng.integers(max_len - 1100, max_len + 1, n).astype(np.int32)
+    p, table, _ = _geom(rng, n, Hq, Hkv, d, dtype, bs, lens, max_blocks=-(-max_len // bs))
+    print(f"\n[case] decode full chip {dtype} {Hq}/{Hkv} d={d} n={n} L={L} max_len={max_len}", flush=True)
+    params = kara.make_params(p, n)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator(device=dev).manual_seed(3)
+    kp, vp, q = (torch.randn(shape, generator=g, device=dev).to(dt)
+                 for shape in [(p["num_pages"], Hkv, bs, d)] * 2 + [(L, n, Hq, d)])
+    T = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(dev)  # noqa: E731
+    out = torch.full((L, n, Hq, d), float("nan"), dtype=torch.float32, device=dev)
+    ws = torch.full((kara.decode_workspace_size(params, n, L, max_len),), 255, dtype=torch.uint8, device=dev)
+    kara.decode_attention(params, T(np.arange(n, dtype=np.int32)), q, [kp] * L, [vp] * L, T(table), T(lens), max_len, out, ws)
+    torch.cuda.synchronize()
+    tab = T(table.astype(np.int64))
+    for j in range(n):
+        pos = torch.arange(int(lens[j]), device=dev)
+        K, V = (t[tab[j][pos // bs], :, pos % bs].double().permute(1, 0, 2).contiguous() for t in (kp, vp))
+        for l in range(L):
+            x = torch.matmul(q[l, j].double().view(Hkv, Hq // Hkv, d) / d ** 0.5, K.transpose(1, 2).contiguous())
+            want = torch.matmul(torch.softmax(x, dim=2), V).view(Hq, d)
+            err = (out[l, j].double() - want).abs()
+            assert bool((err <= 1e-4 + 1e-4 * want.abs()).all()), (l, j, float(err.max()))
+    print("[case] ok", flush=True)
+
+
 @pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f32", 64)])
 def test_kv_append(dtype, d):
     from paper_2607_01237_amd import kara
