@@ -195,8 +195,8 @@ def summarize_pmc(fetch_csv, write_csv, workload, calib_gib):
         blob[stage] = {"kernels": kernels, "hbm_bytes_per_launch": total / passes if passes else None,
                        "sources_sha256": sources_sha256(TRAFFIC_SOURCES[stage])}
     lines += ["", "The table gives the average per dispatch.  Per pass of a stage (one scoring launch; one "
-              "selection-and-compaction pass, selection being one launch in the staged pass and in the fused step "
-              "alike):", "", "```json", json.dumps(blob, indent=1), "```"]
+              "selection-and-compaction pass, over the staged passes and the fused step alike; in the fused step "
+              "selection adds the scoring splits' sums and no split_sum_kernel runs):", "", "```json", json.dumps(blob, indent=1), "```"]
     return "\n".join(lines)
 
 
