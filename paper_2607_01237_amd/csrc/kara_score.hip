@@ -35,6 +35,7 @@
 
 #include "kara_score.h"
 #include "kara_score_dpp.h"
+#include "kara_score_swap.h"
 
 namespace kara {
 namespace {
@@ -758,7 +759,7 @@ void score1_kernel(ScoreArgs a) {
   __shared__ uint32_t qrow_off[kS1BlocksPerSplit * ROWS];
   // keys that changed places (reorder): key swap_key[i] sits at position
   // swap_pos[i] and the other way round; counts of candidates
-  __shared__ uint16_t swap_key[64], swap_pos[64];
+  __shared__ uint16_t swap_key[kSwapMax], swap_pos[kSwapMax];
   __shared__ int swap_cnt[NW];
 
   const Geom& g = a.g;
@@ -1178,12 +1179,12 @@ void score1_kernel(ScoreArgs a) {
       if (li == 0) norm[j] = j < N ? ss : 0.f;
     }
     lds_barrier();
-    // the largest bound (in the norm's upper 16 bits) that 64 keys reach
+    // the largest bound on the ranks that kSwapMax keys reach
     uint32_t bits[kKeys / NTH];
 #pragma unroll
-    for (int i = 0; i < kKeys / NTH; ++i) bits[i] = __float_as_uint(norm[i * NTH + tid_r]) >> 16;
+    for (int i = 0; i < kKeys / NTH; ++i) bits[i] = swap_rank(__float_as_uint(norm[i * NTH + tid_r]));
     uint32_t bound = 0;
-    for (int bit = 14; bit >= 0; --bit) {
+    for (int bit = kSwapRankBits - 1; bit >= 0; --bit) {
       const uint32_t cand = bound | (1u << bit);
       int cnt = 0;
 #pragma unroll
@@ -1193,22 +1194,24 @@ void score1_kernel(ScoreArgs a) {
       int all = 0;
 #pragma unroll
       for (int w = 0; w < NW; ++w) all += swap_cnt[w];
-      if (all >= 64) bound = cand;
+      if (all >= kSwapMax) bound = cand;
       lds_barrier();
     }
-    // wave 0 pairs the keys above it (at most 63) that are outside the first
-    // tiles with the first tiles' other keys, both in ascending order
+    // wave 0 pairs the keys above it (fewer than kSwapMax) that are outside the
+    // first tiles with the first tiles' other keys, both in ascending order
+    static_assert(KQ * 16 == kSwapMax, "a lane of wave 0 per key of the first tiles");
     if (wave == 0) {
       int nk = 0;
       for (int j0 = 0; j0 < kKeys; j0 += 64) {
         const int j = j0 + lane;
-        const bool take = (__float_as_uint(norm[j]) >> 16) > bound && j % (NT * 16) >= 16;
+        const bool take = swap_rank(__float_as_uint(norm[j])) > bound && j % (NT * 16) >= 16;
         const uint64_t mask = __ballot(take);
-        if (take) swap_key[nk + __builtin_popcountll(mask & ((1ull << lane) - 1))] = (uint16_t)j;
+        const int at = nk + __builtin_popcountll(mask & ((1ull << lane) - 1));
+        if (take && at < kSwapMax) swap_key[at] = (uint16_t)j;
         nk += __builtin_popcountll(mask);
       }
       const int p = (lane >> 4) * NT * 16 + (lane & 15);
-      const bool give = p < N && (__float_as_uint(norm[p]) >> 16) <= bound;
+      const bool give = p < N && swap_rank(__float_as_uint(norm[p])) <= bound;
       const uint64_t mask = __ballot(give);
       if (give) swap_pos[__builtin_popcountll(mask & ((1ull << lane) - 1))] = (uint16_t)p;
       if (lane == 0) swap_cnt[0] = min(nk, (int)__builtin_popcountll(mask));

@@ -250,3 +250,36 @@ def test_validation_of_page_tables(num_pages, max_blocks):
     torch.cuda.synchronize()
     assert np.array_equal(st.cpu().numpy(), want), st
     print("[case] ok", flush=True)
+
+
+@pytest.mark.parametrize("window", [513, 1024, 2048])
+def test_keys_of_all_ones_stay_in_their_sequence(window):
+    # a window whose pool rows were never written (0xFF bytes: bf16 NaN with
+    # the sign set) beside a healthy one: its own scores are NaN, the healthy
+    # one's what they are without it, bit for bit
+    import kara_check as kc
+    from paper_2607_01237_amd import kara
+    _need_gpu()
+    print(f"\n[case] window of 0xFF keys, N={window}", flush=True)
+    c = kc.setup(ki.workload("batch8", n_seqs=2, n_layers=1, n_q_heads=4, n_kv_heads=2, window=window, budget=window // 5,
+                             prefix=(0, 60), tail=(0, 9), num_pages=400, key_mode="normal"))
+    p, bs = c.p, c.p["block_size"]
+    ws = torch.empty(kara.workspace_size(c.params, 2, 1), dtype=torch.uint8, device="cuda")
+
+    def scores():
+        out = torch.full((1, 2, p["n_kv_heads"], window), -1.0, device="cuda")
+        st = torch.full((2,), -1, dtype=torch.int32, device="cuda")
+        kara.score_window(c.params, c.trig, c.q, c.kp, c.bt, c.seq_lens, c.win_start, out, st, ws)
+        torch.cuda.synchronize()
+        assert (st == 0).all()
+        return out.cpu()
+
+    before = scores()
+    s = int(c.geom.trig[1])
+    start = int(c.geom.win_start[s])
+    raw = c.kp[0].view(torch.int16)
+    for j in range(start, start + window):
+        raw[int(c.geom.block_table[s, j // bs]), :, j % bs, :] = -1
+    after = scores()
+    assert torch.equal(after[:, 0], before[:, 0])
+    assert after[:, 1].isnan().all()
