@@ -82,7 +82,8 @@ def parse():
 
 TRAFFIC_SOURCES = {
     "score": ["paper_2607_01237_amd/csrc/kara_score.hip", "paper_2607_01237_amd/csrc/kara_score_res.hip",
-              "paper_2607_01237_amd/csrc/kara_score.h", "paper_2607_01237_amd/csrc/kara_score_dpp.h"],
+              "paper_2607_01237_amd/csrc/kara_score.h", "paper_2607_01237_amd/csrc/kara_score_dpp.h",
+              "paper_2607_01237_amd/csrc/kara_lds.h", "paper_2607_01237_amd/csrc/kara_score_swap.h"],
     "select_compact": ["paper_2607_01237_amd/csrc/kara_select.hip", "paper_2607_01237_amd/csrc/kara_pages.hip"],
 }
 TRAFFIC_KERNELS = {"score": ["score1_kernel", "score_kernel", "score_res_kernel", "split_sum_kernel"],

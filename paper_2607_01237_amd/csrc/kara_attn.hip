@@ -28,6 +28,7 @@
 #include <type_traits>
 
 #include "kara_internal.h"
+#include "kara_lds.h"
 #include "kara_recompute.h"
 
 namespace kara {
@@ -102,32 +103,6 @@ __device__ inline float wave_max4(float v) {
   v = fmaxf(v, __shfl_xor(v, 16, 64));
   v = fmaxf(v, __shfl_xor(v, 32, 64));
   return v;
-}
-
-// Direct global->LDS copy of 16 bytes per lane; lane i's bytes land at
-// lds_wave_base + 16*i (global_load_lds_dwordx4, LDS base in M0).  Issued
-// through inline assembly so the compiler adds no wait of its own before
-// LDS reads; the kernel waits explicitly.  M0 is restored.
-__device__ inline void copy16(const void* g, char* lds_wave_base) {
-  const uint32_t lds = __builtin_amdgcn_readfirstlane(
-      (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds_wave_base);
-  uint32_t saved;
-  asm volatile(
-      "s_mov_b32 %0, m0\n\t"
-      "s_mov_b32 m0, %2\n\t"
-      "global_load_lds_dwordx4 %1, off\n\t"
-      "s_mov_b32 m0, %0"
-      : "=&s"(saved)
-      : "v"(g), "s"(lds)
-      : "memory");
-}
-
-// Barrier for LDS traffic only (the copies it covers are waited for first).
-__device__ inline void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
-template <int N>
-__device__ inline void wait_vm() {
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
 // Wait for this thread's copies of a chunk when the copies of `newer` later

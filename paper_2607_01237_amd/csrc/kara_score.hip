@@ -33,6 +33,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "kara_lds.h"
 #include "kara_score.h"
 #include "kara_score_dpp.h"
 #include "kara_score_swap.h"
@@ -130,39 +131,6 @@ __device__ inline float sum16(float v) {
 #pragma unroll
   for (int o = 1; o < 16; o <<= 1) v += __shfl_xor(v, o, 64);
   return v;
-}
-
-// Direct global->LDS copy of 16 bytes per lane; lane i's bytes land at
-// lds_wave_base + 16*i (global_load_lds_dwordx4 with the LDS base in M0).
-// Issued through inline assembly: the compiler then inserts no wait of its
-// own before LDS reads (it cannot tell the ring stages apart and would drain
-// every copy); the kernel waits explicitly with wait_chunks().  M0 is
-// restored.
-__device__ inline void copy16(const void* g, char* lds_wave_base) {
-  const uint32_t lds = __builtin_amdgcn_readfirstlane(
-      (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds_wave_base);
-  uint32_t saved;
-  asm volatile(
-      "s_mov_b32 %0, m0\n\t"
-      "s_mov_b32 m0, %2\n\t"
-      "global_load_lds_dwordx4 %1, off\n\t"
-      "s_mov_b32 m0, %0"
-      : "=&s"(saved)
-      : "v"(g), "s"(lds)
-      : "memory");
-}
-
-// Workgroup barrier for LDS traffic only.  __syncthreads() would also drain
-// every outstanding global->LDS copy (its release fence waits on vmcnt),
-// defeating the prefetch ring; the copies this barrier must cover are waited
-// for explicitly first.
-__device__ inline void lds_barrier() {
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
-template <int N>
-__device__ inline void wait_vm() {
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
 // Wait until at most kL*newer of this thread's memory operations are
@@ -630,13 +598,15 @@ __device__ __forceinline__ int s1_swz(int row) { return ((row & 3) << 2) | ((row
 // moves lane i's bytes from g[j] + voff[j] + 1024 j to LDS address lbase +
 // OFF + 1024 j + 16 i (the instruction offset moves both addresses, so the
 // callers fold its 1024 j out of the wave-uniform bases g[j]).  M0 is formed
-// by one scalar add and left clobbered.
+// by one scalar add, with the wait state its read by the first load needs, and
+// left clobbered.
 template <int OFF, int N>
 __device__ __forceinline__ void copy_n(const uint64_t (&g)[N], const uint32_t (&voff)[N], uint32_t lbase) {
   static_assert(N == 1 || N == 2 || N == 4, "one, two or four copies");
   if constexpr (N == 4)
     asm volatile(
         "s_add_u32 m0, %4, %5\n\t"
+        "s_nop 0\n\t"
         "global_load_lds_dwordx4 %0, %6\n\t"
         "global_load_lds_dwordx4 %1, %7 offset:1024\n\t"
         "global_load_lds_dwordx4 %2, %8 offset:2048\n\t"
@@ -648,6 +618,7 @@ __device__ __forceinline__ void copy_n(const uint64_t (&g)[N], const uint32_t (&
   else if constexpr (N == 2)
     asm volatile(
         "s_add_u32 m0, %2, %3\n\t"
+        "s_nop 0\n\t"
         "global_load_lds_dwordx4 %0, %4\n\t"
         "global_load_lds_dwordx4 %1, %5 offset:1024"
         :
@@ -656,6 +627,7 @@ __device__ __forceinline__ void copy_n(const uint64_t (&g)[N], const uint32_t (&
   else
     asm volatile(
         "s_add_u32 m0, %1, %2\n\t"
+        "s_nop 0\n\t"
         "global_load_lds_dwordx4 %0, %3"
         :
         : "v"(voff[0]), "s"(lbase), "n"(OFF), "s"(g[0])

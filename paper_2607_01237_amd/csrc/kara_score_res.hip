@@ -25,6 +25,7 @@
 // units of 512 keys 579 -> 330 us.
 #include <type_traits>
 
+#include "kara_lds.h"
 #include "kara_score.h"
 #include "kara_score_dpp.h"
 
@@ -61,23 +62,6 @@ struct RCfg {
     return ((row & 3) << 2) | ((row >> 2) & 3);
   }
 };
-
-__device__ inline void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
-// Direct global->LDS copy of 16 bytes per lane to lds_wave_base + 16*lane.
-__device__ inline void copy16(const void* g, char* lds_wave_base) {
-  const uint32_t lds = __builtin_amdgcn_readfirstlane(
-      (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds_wave_base);
-  uint32_t saved;
-  asm volatile(
-      "s_mov_b32 %0, m0\n\t"
-      "s_mov_b32 m0, %2\n\t"
-      "global_load_lds_dwordx4 %1, off\n\t"
-      "s_mov_b32 m0, %0"
-      : "=&s"(saved)
-      : "v"(g), "s"(lds)
-      : "memory");
-}
 
 template <int CTRL>
 __device__ __forceinline__ float dpp(float v) {
@@ -202,7 +186,7 @@ void score_res_kernel(ScoreArgs a) {
     }
   };
   load_q(r0 + rg * 32, qoff);
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  wait_vm<0>();
   lds_barrier();
 
   int koff[KC];
