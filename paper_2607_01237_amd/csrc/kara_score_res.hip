@@ -40,7 +40,12 @@ constexpr int kWaves = kThreads / 64;
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kNegInf = -__builtin_huge_valf();
 constexpr float kMaxFloor = -1e30f;   // finite, so that 2^(-inf - m) is 0 and not NaN
-constexpr float kF32Max = 3.402823466e38f;
+// Row sums past this run again from the exact maximum.  At most 2^60, so that
+// 1 / sum and a weight's share stay normal numbers (v_rcp_f32 and v_exp_f32
+// flush those below 2^-126) and the sum of four key parts cannot overflow; and
+// where two parts' references differ by more than 2^126, which flushes the
+// lower part's factor, its weights are below 2^-66 of the row's sum.
+constexpr float kSumMax = 0x1p60f;
 
 template <int DT, int D, int NTW, int KS>
 struct RCfg {
@@ -318,9 +323,9 @@ void score_res_kernel(ScoreArgs a) {
       // the next rows' queries arrive behind the exchange and the column sums
       if (it + 1 < n_it) load_q(row + C::kRows, qoff);
       const float l_own = reduce_scatter8<false>(L, li);
-      // a logit 128 log2-units above the reference overflows: once more, from
-      // the exact maximum
-      bool bad = __builtin_amdgcn_ballot_w64(!(l_own <= kF32Max)) != 0;
+      // a logit 60 log2-units above the reference: once more, from the exact
+      // maximum
+      bool bad = __builtin_amdgcn_ballot_w64(!(l_own <= kSumMax)) != 0;
       float m_all = m_own, l_all = l_own;
       if constexpr (KS > 1) {
         if (li < 8) xch[par][kq][rg * 32 + own_row] = float2{m_own, l_own};

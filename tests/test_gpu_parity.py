@@ -233,3 +233,53 @@ def test_wide_block_table():
     # the kept rows): the instance that reads the kept indices and the table
     # from global memory for every tile
     _, rep, _ = _run(ki.workload("batch8", n_seqs=2, n_layers=2, max_blocks=8400))
+
+
+@pytest.mark.parametrize("dtype,d,window,part", [
+    ("bf16", 64, 240, 0), ("f32", 128, 100, 0),                                    # one key part
+    ("bf16", 64, 449, 256), ("bf16", 128, 512, 256), ("f32", 128, 256, 128),       # two, of `part` keys
+    ("bf16", 64, 520, 160), ("bf16", 64, 1152, 288),                               # four
+    ("bf16", 64, 1200, 600), ("f32", 64, 600, 300),                                # past the kernel's range: two sweeps
+])
+def test_resident_keys_far_above_their_reference(dtype, d, window, part):
+    # Every query finds one late key far above the first tile, where a wave
+    # takes its reference: up to where its weight nearly overflows fp32 and the
+    # row's 1 / sum lies below the normal range, and past it.  With several
+    # key parts, also beside a part whose reference is as far above the first
+    # part's, so that the two references differ by more than 2^126 while the
+    # late key still holds an eighth of the row.
+    import kara_check as kc
+    from paper_2607_01237_amd import kara
+    _need_gpu()
+    print(f"\n[case] late key far above the reference, {dtype} d={d} N={window}", flush=True)
+    c = kc.setup(ki.workload("batch8", n_seqs=1, n_layers=1, n_q_heads=2, n_kv_heads=1, dtype=dtype, head_dim=d,
+                             window=window, budget=window // 5, chunk_budget=4, max_chunk_len=4, prefix=(5, 5), tail=(3, 3),
+                             num_pages=96, key_mode="normal"))
+    bs, s = c.p["block_size"], int(c.geom.trig[0])
+    rows = [(int(c.geom.block_table[s, j // bs]), j % bs)
+            for j in range(int(c.geom.win_start[s]), int(c.geom.win_start[s]) + window)]
+    # logits = a key's first element (+ about 0.05): 8 * scale * sqrt(d / 64)
+    c.q *= 0.25
+    c.q[..., 0] = 8.0 * (d / 64) ** 0.5
+    c.kp[0] *= 0.25
+    for pg, o in rows:
+        c.kp[0][pg, :, o, 0] = 0.0
+    ws = torch.empty(kara.workspace_size(c.params, 1, 1), dtype=torch.uint8, device="cuda")
+    late = (part if part else window) - 3
+    for high in (40.0, 42.0, 60.0, 75.0, 87.0, 87.5, 88.0, 88.5, 89.0, 100.0):
+        for beside in (None,) if not part else (None, high + 2.0):
+            pg, o = rows[late]
+            c.kp[0][pg, :, o, 0] = high
+            if part:
+                pg, o = rows[part + 2]
+                c.kp[0][pg, :, o, 0] = beside if beside is not None else 0.0
+            c.host = kc.snapshot(c)
+            scores = torch.full((1, 1, 1, window), float("nan"), device="cuda")
+            st = torch.full((1,), -1, dtype=torch.int32, device="cuda")
+            kara.score_window(c.params, c.trig, c.q, c.kp, c.bt, c.seq_lens, c.win_start, scores, st, ws)
+            torch.cuda.synchronize()
+            ora, _ = kc.oracle_scores(c)
+            rep = kc.check_p1(scores.cpu().numpy(), ora)
+            print(f"[case] key at {high}, beside {beside}: {rep}", flush=True)
+            # (2 x window rows, all but a few of their weight on the placed keys)
+            assert ora[0, 0, 0, late] > 0.1 * 2 * window
