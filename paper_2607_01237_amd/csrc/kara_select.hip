@@ -263,10 +263,11 @@ __device__ void argmax_top(const KeyT (&key)[EPT], const bool (&elig)[EPT], bool
       const uint32_t hi = wave_max_u32((uint32_t)(bk >> 32));
       const uint32_t lo = wave_max_u32((uint32_t)(bk >> 32) == hi ? (uint32_t)bk : 0u);
       const uint64_t wk = ((uint64_t)hi << 32) | lo;
-      const uint64_t owners = __ballot(bk == wk);
-      const int src = (int)__builtin_ctzll(owners);
+      // (a lane with nothing left is no owner of key 0, which a score of all
+      // ones, a NaN, maps to)
+      const uint64_t owners = __ballot(bk == wk && bp != 0x7fffffff);
       bk = wk;
-      bp = __builtin_amdgcn_readlane(bp, src);
+      bp = owners ? __builtin_amdgcn_readlane(bp, (int)__builtin_ctzll(owners)) : 0x7fffffff;
     }
     const int slot = r & 1;
     if (lane == 0) {

@@ -94,6 +94,34 @@ def test_select_and_token2chunk_bit_exact(name, scores):
             assert np.array_equal(k1[u], wk), ("one launch", name, budget, alpha, gamma, u)
 
 
+@pytest.mark.parametrize("n", [40, 300, 1100, 2500])
+@pytest.mark.parametrize("budget,alpha,gamma", [(8, 0, 8), (14, 6, 8), (30, 8, 3), (9, 8, 3)])
+def test_selection_of_nan_scores_is_whole(n, budget, alpha, gamma):
+    # scores of pool memory filled with 0xFF: NaN of all ones, the one value
+    # that ranks at key 0.  A set still holds as many positions as it should,
+    # the lowest first among equals: discrete sets, chunks and fills of at most
+    # 8 items take them one at a time, larger ones by radix
+    from paper_2607_01237_amd import kara
+    _need_gpu()
+    p = dict(window=n, buffer=0, budget=budget, chunk_budget=alpha, max_chunk_len=gamma, head_dim=128, n_q_heads=8,
+             n_kv_heads=8, block_size=16, num_pages=64, max_blocks_per_seq=256, dtype="bf16", scale=0.0)
+    par = kara.make_params(p, 1)
+    bits = np.full((2, n), 0xFFFFFFFF, dtype=np.uint32)
+    bits[1, n // 2] = np.float32(1.0).view(np.uint32)       # one score that beats them all
+    sc = _dev(bits.view(np.float32))
+    disc = torch.full((2, budget - alpha), -9, dtype=torch.int32, device="cuda")
+    kept = torch.full((2, budget), -9, dtype=torch.int32, device="cuda")
+    kara.select_kept(par, sc, disc, kept)
+    torch.cuda.synchronize()
+    k = budget - alpha
+    d, kp = disc.cpu().numpy(), kept.cpu().numpy()
+    first = np.delete(np.arange(n), n // 2)
+    assert np.array_equal(d[0], np.arange(k))
+    assert np.array_equal(d[1], np.sort(np.append(first[:k - 1], n // 2)))
+    assert np.array_equal(kp[0], np.arange(budget))
+    assert np.array_equal(kp[1], np.sort(np.append(first[:budget - 1], n // 2)))
+
+
 def test_token2chunk_rejects_bad_discrete():
     from paper_2607_01237_amd import kara
     _need_gpu()
