@@ -251,6 +251,18 @@ kara_status_t kara_workspace_size(const kara_params_t* p, int32_t n_trig, int32_
   return KARA_OK;
 }
 
+// (kara_internal.h: for the tests)
+kara_status_t kara_call_workspace_bytes(const kara_params_t* p, int32_t n_trig, int32_t n_windows, int32_t n_layers,
+                                        size_t* bytes) {
+  Geom g;
+  kara_status_t st = make_geom(p, n_trig, &g);
+  if (st != KARA_OK) return st;
+  if (!bytes || n_layers < 1 || n_windows < 1) return KARA_ERR_INVALID_ARG;
+  g.n_win = n_windows;
+  *bytes = compress_workspace_bytes(g, n_layers);
+  return KARA_OK;
+}
+
 kara_status_t kara_validate(const kara_params_t* p, int32_t n_trig, const int32_t* trig,
                             const int32_t* block_table, const int32_t* seq_lens,
                             const int32_t* win_start, int32_t* status, void* stream) {

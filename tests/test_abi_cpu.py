@@ -2,6 +2,7 @@
 include/kara.h and include/kara_harness.h declare, and its host-side argument checks reject bad calls
 before anything is launched."""
 import ctypes
+import itertools
 import os
 
 import pytest
@@ -59,11 +60,24 @@ def test_workspace_covers_smaller_launches(lib, over):
     # more sequences or layers must hold every smaller launch (a server sizes
     # it once), so the size never falls as units are added
     p = good_params(**over)
-    sizes = [kara.workspace_size(p, n, layers) for layers in (1, 3) for n in list(range(1, 70)) + [100, 127, 128, 129, 300]]
+    counts = list(range(1, 70)) + [100, 127, 128, 129, 300]
+    sizes = [kara.workspace_size(p, n, layers) for layers in (1, 3) for n in counts]
     half = len(sizes) // 2
     for part in (sizes[:half], sizes[half:]):
         assert all(a <= b for a, b in zip(part, part[1:]))
     assert all(kara.workspace_size(p, 3 * n, 1) == kara.workspace_size(p, n, 3) for n in (1, 5, 31))
+    # ... and what a call itself uses, of as many units or fewer, fits it
+    needs = [_call_bytes(lib, p, n, 1, 1) for n in counts]
+    for size, so_far in zip(sizes[:half], itertools.accumulate(needs, max)):
+        assert so_far <= size
+    for n, size in zip(counts, sizes[half:]):
+        assert max(_call_bytes(lib, p, n, 1, 3), _call_bytes(lib, p, 3 * n, 1, 1), _call_bytes(lib, p, n, 3, 1)) <= size
+
+
+def _call_bytes(lib, p, n_trig, n_windows, n_layers):
+    out = ctypes.c_size_t(0)
+    assert lib.kara_call_workspace_bytes(ctypes.byref(p), n_trig, n_windows, n_layers, ctypes.byref(out)) == kara.OK
+    return out.value
 
 
 def test_workspace_size_scales(lib):

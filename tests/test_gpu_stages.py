@@ -311,3 +311,32 @@ def test_keys_of_all_ones_stay_in_their_sequence(window):
     after = scores()
     assert torch.equal(after[:, 0], before[:, 0])
     assert after[:, 1].isnan().all()
+
+
+@pytest.mark.parametrize("over", [dict(window=600), dict(window=1024), dict(window=200), dict(window=300, head_dim=64),
+                                  dict(window=2100, n_q_heads=2, n_kv_heads=1)])
+def test_one_workspace_serves_smaller_calls(over):
+    # a workspace sized for all sequences and layers holds calls of fewer,
+    # which split their rows further: scores as the oracle has them, nothing
+    # written past the size
+    import kara_check as kc
+    from paper_2607_01237_amd import kara
+    _need_gpu()
+    cfg = dict(n_seqs=4, n_layers=2, n_q_heads=4, n_kv_heads=2, budget=over["window"] // 5, prefix=(0, 60), tail=(0, 9),
+               num_pages=1200, key_mode="normal")
+    cfg.update(over)
+    c = kc.setup(ki.workload("batch8", **cfg))
+    print(f"\n[case] one workspace, {over}", flush=True)
+    size = kara.workspace_size(c.params, 4, 2)
+    ws = torch.full((size + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+    ora, _ = kc.oracle_scores(c)
+    for nt, L in ((4, 2), (3, 1), (1, 2), (1, 1)):
+        ws.fill_(0x5A)
+        scores = torch.full((L, nt, c.p["n_kv_heads"], over["window"]), float("nan"), device="cuda")
+        st = torch.full((nt,), -1, dtype=torch.int32, device="cuda")
+        kara.score_window(c.params, c.trig[:nt].contiguous(), c.q[:L, :nt].contiguous(), c.kp[:L], c.bt, c.seq_lens,
+                          c.win_start, scores, st, ws[:size])
+        torch.cuda.synchronize()
+        assert (st == 0).all()
+        kc.check_p1(scores.cpu().numpy(), ora[:L, :nt])
+        assert (ws[size:] == 0x5A).all()
