@@ -656,39 +656,16 @@ __device__ __forceinline__ void static_for(F&& f) {
   }
 }
 
-// Geometry of one single-sweep instance: WAVES waves of RT row tiles each.
-// The keys are split in four quarters (one per SIMD) and the block's rows in
-// WAVES/4 groups; wave w takes key quarter w % 4 and row group w / 4.  Four
-// waves (one per SIMD, 512 registers each) hold 64 rows as one group; eight
-// (two per SIMD, 256 registers each) hold them as two groups of 32, so that
-// two waves share each SIMD's issue slots: a single wave issues a vector
-// instruction at most every ~7 cycles, two together every ~3.5.
-template <int WAVES, int RT>
-struct S1Cfg {
-  static constexpr int kWaves = WAVES;
-  static constexpr int kThreads = 64 * WAVES;
-  static constexpr int kRT = RT;
-  static constexpr int kKQ = 4;                            // key quarters
-  static constexpr int kRG = WAVES / kKQ;                  // row groups
-  static constexpr int kWaveRows = 16 * RT;                // query rows of a wave
-  static constexpr int kRows = kWaveRows * kRG;            // query rows per block
-  // one LDS ring of key tiles per key quarter, shared by its row groups:
-  // each wave copies kCW of a tile's four 1 KB parts, and with more than one
-  // group the waves meet at a barrier before every tile's operands are read
-  static constexpr int kCW = 4 / kRG;                      // copies of a tile per wave
-  // Logits are double-buffered, so a tile's vector work follows the next
-  // tile's MFMAs.  One wave per SIMD also double-buffers the key operands
-  // (read before the MFMAs) and keeps the weights in accumulation registers;
-  // with two, the operands are read between the MFMAs and the vector work,
-  // after the tile's barrier, and the weights fit the ordinary registers.
-  static constexpr bool kAgpr = WAVES == 4;
-  static constexpr int kKbBuf = WAVES == 4 ? 2 : 1;
-  static constexpr int kQCopies = kRows / 4;               // query copies of a block (4 rows each)
-  static constexpr int kQMax = (kQCopies + WAVES - 1) / WAVES;   // per wave, at most
-  static constexpr int kQMin = kQCopies / WAVES;                   // per wave, at least
-  static_assert(kQMin >= 1, "every wave copies part of the queries");
-  static_assert(WAVES % kKQ == 0 && kRG >= 1 && 4 % kRG == 0, "whole row groups, whole copies");
-};
+// A workgroup of the single-sweep kernel: four waves, one per SIMD with 512
+// registers each, hold 64 query rows (four row tiles) and a quarter of the
+// keys each.  Logits and key operands are double-buffered, so a tile's vector
+// work follows the next tile's MFMAs.
+constexpr int kS1Waves = 4;                       // one key quarter each
+constexpr int kS1Threads = 64 * kS1Waves;
+constexpr int kS1RT = 4;                          // row tiles of 16
+constexpr int kS1Rows = 16 * kS1RT;               // query rows per block
+constexpr int kS1Copies = 4;                      // 1 KB copies of a key tile
+constexpr int kS1QCopies = kS1Rows / 4 / kS1Waves;   // query copies (4 rows each) of a block per wave
 
 // Key tiles in a wave's LDS ring: the most, up to 8, that divide the NT tiles
 // of a block (the ring's stage is then a constant of the unrolled loop).
@@ -705,25 +682,24 @@ constexpr int s1_stages(int nt) {
 // tile's vector work with the next one's matrix work (30 sequences x 8 layers,
 // N = 736: 2.21 ms with the tiles skipped in a 16-tile instance, 1.84 ms
 // with all of 12 worked).
-template <class CF, int NT, bool FULL>
-__global__ __launch_bounds__(CF::kThreads) __attribute__((amdgpu_waves_per_eu(CF::kWaves / 4, CF::kWaves / 4)))
+template <int NT, bool FULL>
+__global__ __launch_bounds__(kS1Threads) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void score1_kernel(ScoreArgs a) {
   constexpr int S = s1_stages(NT);
   constexpr int D = S - 1;                                 // tiles copied ahead of the one being read
-  constexpr int RT = CF::kRT;
-  constexpr int NW = CF::kWaves;
-  constexpr int ROWS = CF::kRows;
-  constexpr int NTH = CF::kThreads;
-  constexpr int KQ = CF::kKQ;
-  constexpr int WROWS = CF::kWaveRows;
+  constexpr int RT = kS1RT;
+  constexpr int NW = kS1Waves;
+  constexpr int ROWS = kS1Rows;
+  constexpr int NTH = kS1Threads;
+  constexpr int CW = kS1Copies;
   static_assert(NT % S == 0 && NT % 4 == 0 && D >= 4, "tiles per wave: a multiple of the ring and of 4");
-  __shared__ __attribute__((aligned(16))) char kring[CF::kKQ][S][kS1TileBytes];
+  __shared__ __attribute__((aligned(16))) char kring[NW][S][kS1TileBytes];
   __shared__ __attribute__((aligned(16))) char qbuf[ROWS * kS1RowBytes];
   // byte offset of key j's row in the K pool; entries past N repeat key 0
-  __shared__ uint32_t key_off[KQ * NT * 16];
+  __shared__ uint32_t key_off[NW * NT * 16];
   // per key quarter: row maxima of the first tiles, row sums
-  __shared__ __attribute__((aligned(16))) float smax[KQ][ROWS];
-  __shared__ __attribute__((aligned(16))) float ssum[KQ][ROWS];
+  __shared__ __attribute__((aligned(16))) float smax[NW][ROWS];
+  __shared__ __attribute__((aligned(16))) float ssum[NW][ROWS];
   // per wave: a row sum of the block reached fp16's largest value
   __shared__ __attribute__((aligned(16))) int sbad[NW];
   // byte offset of each of the split's query rows in the unit's queries
@@ -740,10 +716,6 @@ void score1_kernel(ScoreArgs a) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int gq = lane >> 4;
   const int li = lane & 15;
-  const int kq = wave % KQ;              // key quarter
-  const int rg = wave / KQ;              // row group
-  const int rbase = rg * WROWS;          // first block row of this wave
-  constexpr int CW = CF::kCW;
 
   // the row splits of one unit run together on one XCD (its L2 keeps the keys)
   int64_t bid = blockIdx.x;
@@ -772,11 +744,11 @@ void score1_kernel(ScoreArgs a) {
   const int bps = a.rows_split / ROWS;                        // at most kS1BlocksPerSplit
   const int b0 = split * bps;
   const int b1 = min(nblk, b0 + bps);
-  const int wt0 = kq * NT;                                    // this wave's first tile
+  const int wt0 = wave * NT;                                  // this wave's first tile
 
   {
     const int32_t* row_pages = a.bt + (int64_t)s * g.max_blocks;
-    for (int j = tid; j < KQ * NT * 16; j += NTH) {
+    for (int j = tid; j < NW * NT * 16; j += NTH) {
       const int pos = p0 + (j < N ? j : 0);
       const uint64_t row = ((uint64_t)row_pages[pos / g.bs] * g.Hkv + h) * g.bs + pos % g.bs;
       key_off[j] = (uint32_t)(row * kS1RowBytes);
@@ -795,14 +767,13 @@ void score1_kernel(ScoreArgs a) {
   // li ^ (gq << 2) ^ r; a row's byte offset is a multiple of 256, so the
   // source is row offset ^ chunk byte offset (one three-way XOR).
   const uint32_t cbase = (uint32_t)((li ^ (gq << 2)) << 4);
-  // (this wave's copies of a tile: r = rg*CW .. rg*CW + CW-1)
   uint32_t coff[CW];
   auto read_offsets = [&](int tile) __attribute__((always_inline)) {
 #pragma unroll
-    for (int r = 0; r < CW; ++r) coff[r] = key_off[(wt0 + tile) * 16 + 4 * (rg * CW + r) + gq];
+    for (int r = 0; r < CW; ++r) coff[r] = key_off[(wt0 + tile) * 16 + 4 * r + gq];
   };
   const uint32_t ring_base = __builtin_amdgcn_readfirstlane(
-      (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)&kring[kq][0][0]);
+      (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)&kring[wave][0][0]);
   const uint32_t qbuf_base = __builtin_amdgcn_readfirstlane(
       (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)&qbuf[0]);
   // (one M0 per tile: copy j's base folds out the 1024 j its offset adds)
@@ -811,28 +782,24 @@ void score1_kernel(ScoreArgs a) {
 #pragma unroll
   for (int j = 0; j < CW; ++j) {
     kbase[j] = (uint64_t)(uintptr_t)kpool - 1024 * j;
-    cxor[j] = cbase ^ ((uint32_t)(rg * CW + j) << 4);
+    cxor[j] = cbase ^ ((uint32_t)j << 4);
   }
-  const uint32_t kring_part = ring_base + rg * CW * 1024;
   auto issue_k = [&](auto stage_c) __attribute__((always_inline)) {
     constexpr int stage = decltype(stage_c)::value;
     uint32_t vo[CW];
 #pragma unroll
     for (int j = 0; j < CW; ++j) vo[j] = coff[j] ^ cxor[j];
-    copy_n<stage * kS1TileBytes>(kbase, vo, kring_part);
+    copy_n<stage * kS1TileBytes>(kbase, vo, ring_base);
   };
   // the query rows of block blk (rows past R repeat row 0), 4 rows a copy:
   // wave w issues copies w, w + NW, ...; copy cq holds rows 4cq + gq
   auto issue_q = [&](int blk) __attribute__((always_inline)) {
-    static_for<0, CF::kQMax>([&](auto r_c) __attribute__((always_inline)) {
-      constexpr int r = decltype(r_c)::value;
-      const int cq = wave + r * NW;
-      if (r < CF::kQMin || cq < CF::kQCopies) {
-        const int rr = 4 * cq + gq;
-        const uint64_t qb[1] = {(uint64_t)(uintptr_t)qunit};
-        const uint32_t qoff[1] = {qrow_off[(blk - b0) * ROWS + rr] + (uint32_t)((li ^ s1_swz(rr & 15)) * 16)};
-        copy_n<0>(qb, qoff, qbuf_base + cq * 1024);
-      }
+    static_for<0, kS1QCopies>([&](auto r_c) __attribute__((always_inline)) {
+      const int cq = wave + decltype(r_c)::value * NW;
+      const int rr = 4 * cq + gq;
+      const uint64_t qb[1] = {(uint64_t)(uintptr_t)qunit};
+      const uint32_t qoff[1] = {qrow_off[(blk - b0) * ROWS + rr] + (uint32_t)((li ^ s1_swz(rr & 15)) * 16)};
+      copy_n<0>(qb, qoff, qbuf_base + cq * 1024);
     });
   };
 
@@ -851,7 +818,7 @@ void score1_kernel(ScoreArgs a) {
   read_offsets(D % NT);
 
   bf16x8 qa[RT][4];                // [row tile][k step]
-  bf16x8 kb[CF::kKbBuf][4];        // key operands
+  bf16x8 kb[2][4];                 // key operands
   floatx4 acc[2][RT];              // logits: [buffer][row tile], rows 4gq+q, key li
   float m[RT][4], L[RT][4];
   // fp16 weights in pairs of the same row from tiles 2s and 2s+1:
@@ -867,7 +834,7 @@ void score1_kernel(ScoreArgs a) {
   for (int j = 0; j < NT / 4; ++j) colacc[j] = 0.f;
 
   auto kread = [&](int stage, int b) __attribute__((always_inline)) {
-    const char* sb = &kring[kq][stage][0];
+    const char* sb = &kring[wave][stage][0];
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
       const uint4 v = *(const uint4*)(sb + koff[ks]);
@@ -913,10 +880,7 @@ void score1_kernel(ScoreArgs a) {
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         L[rt][q] = s[q];
-        // one wave per SIMD keeps them in accumulation registers; with two
-        // waves (256 registers each) everything fits the ordinary ones
-        if constexpr (CF::kAgpr) es[sp][rt][q] = s1_to_agpr(hp[q]);
-        else es[sp][rt][q] = hp[q];
+        es[sp][rt][q] = s1_to_agpr(hp[q]);
       }
     }
   };
@@ -942,56 +906,24 @@ void score1_kernel(ScoreArgs a) {
   // row reference from every wave's maxima mx of the raw logits, per lane
   // (c > 0, so the maximum of x = logit * c is c times theirs)
   auto share_max = [&](float (&mx)[RT][4]) __attribute__((always_inline)) {
-    if constexpr (RT == 4) {
-      // lane li holds row (li >> 2, 4gq + (li & 3))'s maximum: it forms that
-      // row's reference from every wave's, and the wave shares the 64
-      // through its own row of ssum (no wave reads ssum between a block's
-      // sum exchange and the next one, which this barrier precedes; LDS
-      // operations of a wave complete in order)
-      const int rrow = rbase + (li >> 2) * 16 + 4 * gq + (li & 3);
-      smax[kq][rrow] = reduce_scatter16<true>(reinterpret_cast<float(&)[16]>(mx), li);
-      lds_barrier();
-      static_assert(KQ == 4, "four key quarters");
-      const float v = s1_max3(s1_max3(smax[0][rrow], smax[1][rrow], smax[2][rrow]), smax[3][rrow], smax[3][rrow]);
-      ssum[kq][rrow] = fmaf(v, c, -kS1Headroom);
-#pragma unroll
-      for (int rt = 0; rt < RT; ++rt) {
-        const float4 mm = *(const float4*)&ssum[kq][rbase + rt * 16 + 4 * gq];
-        m[rt][0] = mm.x;
-        m[rt][1] = mm.y;
-        m[rt][2] = mm.z;
-        m[rt][3] = mm.w;
-      }
-      return;
-    } else {
-      if constexpr (RT == 2) {
-        dpp_reduce16xn<true, RT * 4>(reinterpret_cast<float(&)[RT * 4]>(mx));
-      } else {
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) mx[rt][q] = dpp_max16(mx[rt][q]);
-      }
-      if (li == 0) {
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt)
-          *(float4*)&smax[kq][rbase + rt * 16 + 4 * gq] = float4{mx[rt][0], mx[rt][1], mx[rt][2], mx[rt][3]};
-      }
-    }
+    // lane li holds row (li >> 2, 4gq + (li & 3))'s maximum: it forms that
+    // row's reference from every wave's, and the wave shares the 64
+    // through its own row of ssum (no wave reads ssum between a block's
+    // sum exchange and the next one, which this barrier precedes; LDS
+    // operations of a wave complete in order)
+    const int rrow = (li >> 2) * 16 + 4 * gq + (li & 3);
+    smax[wave][rrow] = reduce_scatter16<true>(reinterpret_cast<float(&)[16]>(mx), li);
     lds_barrier();
+    static_assert(NW == 4, "four key quarters");
+    const float v = s1_max3(s1_max3(smax[0][rrow], smax[1][rrow], smax[2][rrow]), smax[3][rrow], smax[3][rrow]);
+    ssum[wave][rrow] = fmaf(v, c, -kS1Headroom);
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
-      float4 v = *(const float4*)&smax[0][rbase + rt * 16 + 4 * gq];
-#pragma unroll
-      for (int w = 1; w < KQ; w += 2) {
-        const float4 o = *(const float4*)&smax[w][rbase + rt * 16 + 4 * gq];
-        const float4 p = w + 1 < KQ ? *(const float4*)&smax[w + 1][rbase + rt * 16 + 4 * gq] : o;
-        v = float4{s1_max3(v.x, o.x, p.x), s1_max3(v.y, o.y, p.y), s1_max3(v.z, o.z, p.z), s1_max3(v.w, o.w, p.w)};
-      }
-      m[rt][0] = fmaf(v.x, c, -kS1Headroom);
-      m[rt][1] = fmaf(v.y, c, -kS1Headroom);
-      m[rt][2] = fmaf(v.z, c, -kS1Headroom);
-      m[rt][3] = fmaf(v.w, c, -kS1Headroom);
+      const float4 mm = *(const float4*)&ssum[wave][rt * 16 + 4 * gq];
+      m[rt][0] = mm.x;
+      m[rt][1] = mm.y;
+      m[rt][2] = mm.z;
+      m[rt][3] = mm.w;
     }
   };
 
@@ -1004,18 +936,14 @@ void score1_kernel(ScoreArgs a) {
   // and the next block's queries when copied in between
   auto wait_next = [&](auto it_c) __attribute__((always_inline)) {
     constexpr int it = decltype(it_c)::value;
-    if constexpr (kS1QIt <= it - 1 && it + 1 <= kS1QIt + D) wait_vm<CW * (D - 2) + CF::kQMin>();
+    if constexpr (kS1QIt <= it - 1 && it + 1 <= kS1QIt + D) wait_vm<CW * (D - 2) + kS1QCopies>();
     else wait_vm<CW * (D - 2)>();
-    // the other row groups' parts of the tile
-    if constexpr (CF::kRG > 1) lds_barrier();
   };
 
   // One pass over the block's key tiles.  Iteration it: logits of tile it,
   // weights of tile it-1, operands of tile it+1 (the next block's tile 0 at
-  // the end), copies of tile it+D into the stage tile it-1 left.  With one
-  // wave per SIMD the operands are read first, into the other buffer; with
-  // two, after the logits' MFMAs are issued (and the tile's barrier), so the
-  // weights' vector work overlaps both the MFMAs and the reads.
+  // the end; read first, into the other buffer), copies of tile it+D into the
+  // stage tile it-1 left.
   auto run_block = [&](bool m_given, int blk) __attribute__((always_inline)) {
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt)
@@ -1027,19 +955,12 @@ void score1_kernel(ScoreArgs a) {
     }
     static_for<0, NT>([&](auto it_c) __attribute__((always_inline)) {
       constexpr int it = decltype(it_c)::value;
-      constexpr int b = it & 1;                             // logits of tile it
+      constexpr int b = it & 1;                             // logits and operands of tile it
       constexpr int bp = b ^ 1;                             // of tile it-1
-      constexpr int kbi = CF::kKbBuf == 2 ? (it & 1) : 0;   // operands of tile it
-      if constexpr (CF::kKbBuf == 2) {
-        wait_next(it_c);
-        kread((it + 1) % S, kbi ^ 1);
-      }
+      wait_next(it_c);
+      kread((it + 1) % S, bp);
       set_zq(it);
-      form(b, kbi);
-      if constexpr (CF::kKbBuf == 1) {
-        wait_next(it_c);
-        kread((it + 1) % S, 0);
-      }
+      form(b, b);
       if constexpr (it == 1) {
         // the shared reference, from every wave's tile 0
         if (!m_given) {
@@ -1065,7 +986,6 @@ void score1_kernel(ScoreArgs a) {
   // exact row maxima over this wave's keys, read straight from the pool (the
   // next tile's keys in flight while this one's logits form)
   auto exact_max = [&]() {
-    constexpr int kOdd = CF::kKbBuf - 1;
     float mx[RT][4];
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt)
@@ -1091,14 +1011,10 @@ void score1_kernel(ScoreArgs a) {
     gread(0, 0);
 #pragma unroll 1
     for (int tile = 0; tile < NT; tile += 2) {
-      if constexpr (kOdd == 1) gread(tile + 1, 1);
+      gread(tile + 1, 1);
       raise(tile, 0);
-      if constexpr (kOdd == 0) gread(tile + 1, 0);
-      else if (tile + 2 < NT) gread(tile + 2, 0);
-      raise(tile + 1, kOdd);
-      if constexpr (kOdd == 0) {
-        if (tile + 2 < NT) gread(tile + 2, 0);
-      }
+      if (tile + 2 < NT) gread(tile + 2, 0);
+      raise(tile + 1, 1);
     }
     share_max(mx);
     // kb[0] is the next pass's tile 0 again, from its stage
@@ -1119,8 +1035,7 @@ void score1_kernel(ScoreArgs a) {
   int n_swap = 0;
   bool reordered = false;
   auto reorder = [&]() {
-    static_assert(CF::kRG == 1, "a wave's column sums are its keys' alone");
-    constexpr int kKeys = KQ * NT * 16;
+    constexpr int kKeys = NW * NT * 16;
     // (opaque, so that nothing below is kept in registers across the blocks)
     int tid_r = tid;
     asm volatile("" : "+v"(tid_r));
@@ -1171,7 +1086,7 @@ void score1_kernel(ScoreArgs a) {
     }
     // wave 0 pairs the keys above it (fewer than kSwapMax) that are outside the
     // first tiles with the first tiles' other keys, both in ascending order
-    static_assert(KQ * 16 == kSwapMax, "a lane of wave 0 per key of the first tiles");
+    static_assert(NW * 16 == kSwapMax, "a lane of wave 0 per key of the first tiles");
     if (wave == 0) {
       int nk = 0;
       for (int j0 = 0; j0 < kKeys; j0 += 64) {
@@ -1213,50 +1128,22 @@ void score1_kernel(ScoreArgs a) {
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks) {
         const uint4 v =
-            *(const uint4*)(qbuf + (rbase + rt * 16 + li) * kS1RowBytes + (((gq * 4 + ks) ^ s1_swz(li)) * 16));
+            *(const uint4*)(qbuf + (rt * 16 + li) * kS1RowBytes + (((gq * 4 + ks) ^ s1_swz(li)) * 16));
         __builtin_memcpy(&qa[rt][ks], &v, 16);
       }
-    float ltot[RT][4];
-    float lrow = 0.f;   // (four row tiles) the total of this lane's row of the reduce-scatter
+    float lrow = 0.f;   // the total of this lane's row of the reduce-scatter
     bool m_given = false;
     for (int pass = 0; pass < 2; ++pass) {
       run_block(m_given, blk);
       // this wave's row sums, then every wave's; a wave's overflow flag:
       // any of its row sums reached fp16's largest value (rows past R repeat
       // row 0, so they overflow only where row 0 did)
-      bool over;
-      if constexpr (RT == 4) {
-        // lane li holds row (li >> 2, 4gq + (li & 3))'s sum (NaN, never
-        // below fp16's largest value, where the selector product met an
-        // infinity)
-        const float r = reduce_scatter16<false>(reinterpret_cast<float(&)[16]>(L), li);
-        ssum[kq][rbase + (li >> 2) * 16 + 4 * gq + (li & 3)] = r * (1.f / kS1WScale);
-        over = !(r < kF16Max);
-      } else {
-        if constexpr (RT == 2) {
-          dpp_reduce16xn<false, RT * 4>(reinterpret_cast<float(&)[RT * 4]>(L));
-        } else {
-#pragma unroll
-          for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) L[rt][q] = dpp_sum16(L[rt][q]);
-        }
-        if (li == 0) {
-          constexpr float s = 1.f / kS1WScale;
-#pragma unroll
-          for (int rt = 0; rt < RT; ++rt)
-            *(float4*)&ssum[kq][rbase + rt * 16 + 4 * gq] =
-                float4{L[rt][0] * s, L[rt][1] * s, L[rt][2] * s, L[rt][3] * s};
-        }
-        // (each sum on its own: a row tile's sums are all NaN where two of
-        // its values overflowed, 0 times infinity in the selector product,
-        // and a maximum would pass over them)
-        over = false;
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) over |= !(L[rt][q] < kF16Max);
-      }
+      // Lane li holds row (li >> 2, 4gq + (li & 3))'s sum (NaN, never
+      // below fp16's largest value, where the selector product met an
+      // infinity)
+      const float r = reduce_scatter16<false>(reinterpret_cast<float(&)[16]>(L), li);
+      ssum[wave][(li >> 2) * 16 + 4 * gq + (li & 3)] = r * (1.f / kS1WScale);
+      const bool over = !(r < kF16Max);
       {
         const bool wbad = __builtin_amdgcn_ballot_w64(over) != 0;
         if (lane == 0) sbad[wave] = wbad;
@@ -1272,30 +1159,10 @@ void score1_kernel(ScoreArgs a) {
         anybad |= f.x | f.y | f.z | f.w;
       }
       if (__builtin_amdgcn_readfirstlane(anybad) == 0) {
-        if constexpr (RT == 4) {
-          const int row = rbase + (li >> 2) * 16 + 4 * gq + (li & 3);
-          lrow = ssum[0][row];
+        const int row = (li >> 2) * 16 + 4 * gq + (li & 3);
+        lrow = ssum[0][row];
 #pragma unroll
-          for (int w = 1; w < KQ; ++w) lrow += ssum[w][row];
-          break;
-        }
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-          float4 v[KQ];
-#pragma unroll
-          for (int w = 0; w < KQ; ++w) v[w] = *(const float4*)&ssum[w][rbase + rt * 16 + 4 * gq];
-          ltot[rt][0] = v[0].x;
-          ltot[rt][1] = v[0].y;
-          ltot[rt][2] = v[0].z;
-          ltot[rt][3] = v[0].w;
-#pragma unroll
-          for (int w = 1; w < KQ; ++w) {
-            ltot[rt][0] += v[w].x;
-            ltot[rt][1] += v[w].y;
-            ltot[rt][2] += v[w].z;
-            ltot[rt][3] += v[w].w;
-          }
-        }
+        for (int w = 1; w < NW; ++w) lrow += ssum[w][row];
         break;
       }
       if (!reordered && blk - b0 < kS1ReorderBlocks) {
@@ -1315,25 +1182,22 @@ void score1_kernel(ScoreArgs a) {
     // parity li >> 3 and 0 to the others, the high fp16 part for even li and
     // the low part for odd li.  Output rows 4gq'+i then hold, for key li',
     // the high (i even) or low (i odd) sum of tile 2s + (gq' >> 1), so a lane
-    // adds its own first two results.  (A lane's part of a weight goes to
-    // the low or high half of its word by a shift; even lanes take the high
-    // fp16 part, odd lanes what it leaves.)
-    const uint32_t half_shift = (uint32_t)(li >> 3) * 16;
-    const bool low_part = (li & 1) != 0;
-    const bool last_block = (blk + 1) * ROWS > R;
-    // Four row tiles: each lane forms the weight of its one row of the
-    // reduce-scatter as an fp16 pair (high | low << 16), and the wave
-    // shares the pairs through its own row of smax (free until the next
-    // block's exchange; LDS operations of a wave complete in order); a
-    // lane's A-operand word is then one byte permutation of a pair.
+    // adds its own first two results.
+    // Each lane forms the weight of its one row of the reduce-scatter as an
+    // fp16 pair (high | low << 16), and the wave shares the pairs through its
+    // own row of smax (free until the next block's exchange; LDS operations of
+    // a wave complete in order); a lane's A-operand word is then one byte
+    // permutation of a pair.  (The exchanged sums carry 2^-21, so 1 / sum is
+    // the scaled weight.)
     uint32_t wrow[RT][4];
-    if constexpr (RT == 4) {
-      const int rrow = (li >> 2) * 16 + 4 * gq + (li & 3);   // the lane's row within the wave's rows
+    {
+      const int rrow = (li >> 2) * 16 + 4 * gq + (li & 3);   // the lane's row
       float w = __builtin_amdgcn_rcpf(lrow);
-      if (last_block && blk * ROWS + rbase + rrow >= R) w = 0.f;   // rows past R weigh nothing
+      // rows past R weigh nothing
+      if ((blk + 1) * ROWS > R && blk * ROWS + rrow >= R) w = 0.f;
       const _Float16 hi = (_Float16)w;
       const _Float16 lo = (_Float16)(w - (float)hi);
-      uint32_t* share = (uint32_t*)&smax[kq][rbase];
+      uint32_t* share = (uint32_t*)&smax[wave][0];
       share[rrow] = (uint32_t)__builtin_bit_cast(uint16_t, hi) | ((uint32_t)__builtin_bit_cast(uint16_t, lo) << 16);
       // bytes of the pair into the word: the high part (even li) or the low
       // part (odd li), at the low (li < 8) or high half
@@ -1347,29 +1211,6 @@ void score1_kernel(ScoreArgs a) {
         wrow[rt][3] = __builtin_amdgcn_perm(p.w, p.w, sel);
       }
     }
-    // (the exchanged sums carry 2^-21, so 1 / sum is the scaled weight)
-    auto weights_of = [&](int rt, uint32_t (&wa)[4]) __attribute__((always_inline)) {
-      if constexpr (RT == 4) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) wa[q] = wrow[rt][q];
-        return;
-      }
-      float wt[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) wt[q] = __builtin_amdgcn_rcpf(ltot[rt][q]);
-      if (last_block) {   // (uniform) rows past R weigh nothing
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          if (blk * ROWS + rbase + rt * 16 + 4 * gq + q >= R) wt[q] = 0.f;
-      }
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const float w = wt[q];
-        const float hi = (float)(_Float16)w;
-        const _Float16 part = (_Float16)(w - (low_part ? hi : 0.f));
-        wa[q] = (uint32_t)__builtin_bit_cast(uint16_t, part) << half_shift;
-      }
-    };
     auto mfma_w = [&](const uint32_t (&wa)[4], int sp, int rt, floatx4 cin) __attribute__((always_inline)) {
       const uint4 av = {wa[0], wa[1], wa[2], wa[3]};
       const uint4 ev = {es[sp][rt][0], es[sp][rt][1], es[sp][rt][2], es[sp][rt][3]};
@@ -1389,33 +1230,14 @@ void score1_kernel(ScoreArgs a) {
     floatx4 cs[NT / 2];
     static_for<0, RT>([&](auto rt_c) __attribute__((always_inline)) {
       constexpr int rt = decltype(rt_c)::value;
-      uint32_t wa[4];
-      weights_of(rt, wa);
       static_for<0, NT / 2>([&](auto s_c) __attribute__((always_inline)) {
         constexpr int sp = decltype(s_c)::value;
-        cs[sp] = mfma_w(wa, sp, rt, rt == 0 ? floatx4{0.f, 0.f, 0.f, 0.f} : cs[sp]);
+        cs[sp] = mfma_w(wrow[rt], sp, rt, rt == 0 ? floatx4{0.f, 0.f, 0.f, 0.f} : cs[sp]);
       });
     });
     static_for<0, NT / 2>([&](auto s_c) __attribute__((always_inline)) { add_pair(s_c, cs[decltype(s_c)::value]); });
   }
   wait_vm<0>();
-  if constexpr (CF::kRG > 1) {
-    // the row groups' column sums of one key quarter, added through its
-    // ring once every wave's copies have landed
-    static_assert((CF::kRG - 1) * NT / 4 * 64 * 4 <= S * kS1TileBytes, "column sums fit a ring");
-    lds_barrier();
-    float* part = (float*)&kring[kq][0][0];
-    if (rg != 0) {
-#pragma unroll
-      for (int j = 0; j < NT / 4; ++j) part[((rg - 1) * (NT / 4) + j) * 64 + lane] = colacc[j];
-    }
-    lds_barrier();
-    if (rg != 0) return;
-#pragma unroll
-    for (int r = 1; r < CF::kRG; ++r)
-#pragma unroll
-      for (int j = 0; j < NT / 4; ++j) colacc[j] += part[((r - 1) * (NT / 4) + j) * 64 + lane];
-  }
   // colacc[j] of lane (gq, li): pair 2j + (gq & 1), tile 2(2j + (gq & 1)) + (gq >> 1)
 #pragma unroll
   for (int j = 0; j < NT / 4; ++j) {
@@ -1477,7 +1299,6 @@ hipError_t launch_d(const ScoreArgs& a, int rt, hipStream_t stream) {
 }
 
 // The single-sweep instance the launches use.
-using S1Use = S1Cfg<4, 4>;
 
 // Tiles per wave of the single-sweep kernel for g, 0 where the two-sweep
 // kernel runs: bf16 with d = 128 and 512 < N <= 2048 (its weights of the
@@ -1488,7 +1309,7 @@ int single_sweep_tiles(const Geom& g) {
   if ((uint64_t)g.num_pages * g.Hkv * g.bs * kS1RowBytes > 0xffffffffull) return 0;
   if ((uint64_t)g.Wq * g.Hq * kS1RowBytes > 0xffffffffull) return 0;
   // the smallest instance (a multiple of 4 tiles per wave) holding the keys
-  return (g.N + 16 * S1Use::kKQ * 4 - 1) / (16 * S1Use::kKQ * 4) * 4;
+  return (g.N + 16 * kS1Waves * 4 - 1) / (16 * kS1Waves * 4) * 4;
 }
 
 // Query rows per workgroup: kS1BlocksPerSplit blocks, the start-up (key
@@ -1498,7 +1319,7 @@ int single_sweep_tiles(const Geom& g) {
 // 4 us).  1 sequence, one layer, W = 1000, 32/8 heads: 116 us in workgroups of
 // 16 blocks, 27 us in ones of 2.
 int single_sweep_rows(const Geom& g, int nt, int64_t n_units) {
-  const int64_t nblk = ((int64_t)g.G * g.Wq + S1Use::kRows - 1) / S1Use::kRows;
+  const int64_t nblk = ((int64_t)g.G * g.Wq + kS1Rows - 1) / kS1Rows;
   const int64_t s0 = (nblk + kS1BlocksPerSplit - 1) / kS1BlocksPerSplit;
   int64_t best = (nblk + s0 - 1) / s0, best_t = -1;
   for (int64_t s = s0; s <= nblk && (s == s0 || s * n_units <= kSplitMaxWgs); ++s) {
@@ -1506,21 +1327,21 @@ int single_sweep_rows(const Geom& g, int nt, int64_t n_units) {
     const int64_t t = (used * n_units + kScoreCUs - 1) / kScoreCUs * (60 + bps * (20 + 3 * nt)) + (used > 1 ? 40 : 0);
     if (best_t < 0 || t < best_t) best_t = t, best = bps;
   }
-  return (int)best * S1Use::kRows;
+  return (int)best * kS1Rows;
 }
 
 template <int NT>
 void launch_s1(const ScoreArgs& a, hipStream_t stream) {
-  const dim3 grid((unsigned)a.n_blocks), block(S1Use::kThreads);
+  const dim3 grid((unsigned)a.n_blocks), block(kS1Threads);
   // (whole instances for the power-of-two window lengths: they save the
   // few instructions that watch for the last key)
   if constexpr (NT % 8 == 0) {
-    if (a.g.N == S1Use::kKQ * 16 * NT) {
-      hipLaunchKernelGGL((score1_kernel<S1Use, NT, true>), grid, block, 0, stream, a);
+    if (a.g.N == kS1Waves * 16 * NT) {
+      hipLaunchKernelGGL((score1_kernel<NT, true>), grid, block, 0, stream, a);
       return;
     }
   }
-  hipLaunchKernelGGL((score1_kernel<S1Use, NT, false>), grid, block, 0, stream, a);
+  hipLaunchKernelGGL((score1_kernel<NT, false>), grid, block, 0, stream, a);
 }
 
 }  // namespace
@@ -1545,7 +1366,7 @@ int64_t max_partial_rows(const Geom& g, int64_t n_units) {
   // kSplitMaxWgs workgroups)
   const int64_t rows = (int64_t)g.G * g.Wq;
   const ScorePlan sp = plan_score(g, std::max<int64_t>(n_units, kSplitMaxWgs + 1));
-  const int64_t least = sp.resident ? 32 : sp.single_nt ? S1Use::kRows : kScoreWaves * 16;
+  const int64_t least = sp.resident ? 32 : sp.single_nt ? kS1Rows : kScoreWaves * 16;
   const int64_t far = n_units * ((rows + least - 1) / least);
   return std::max(sp.n_splits > 1 ? n_units * sp.n_splits : 0, std::min(far, (int64_t)kSplitMaxWgs));
 }

@@ -17,18 +17,13 @@ __device__ __forceinline__ float dpp_reduce16(float v, Op op) {
   v = op(v, __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x140, 0xF, 0xF, false)));
   return v;
 }
-__device__ __forceinline__ float dpp_max16(float v) {
-  return dpp_reduce16(v, [](float x, float y) { return fmaxf(x, y); });
-}
 __device__ __forceinline__ float dpp_sum16(float v) {
   return dpp_reduce16(v, [](float x, float y) { return x + y; });
 }
 
-// The same butterflies for 8 or 16 values at once, one DPP step over all of
-// them before the next (so no step reads a value written fewer than 8
-// instructions before; the leading s_nop covers the values' last writes
-// before the block).  Written as instructions because the compiler keeps a
-// separate DPP move per step, and in IEEE mode adds a quieting max before
+// One DPP step over 8 values at once (the leading s_nop covers the values' last
+// writes before the block).  Written as instructions because the compiler keeps
+// a separate DPP move per step, and in IEEE mode adds a quieting max before
 // every fmaxf.
 #define S1_DPP8(OP, PAT)                                                                               \
   asm volatile("s_nop 1\n\t"                                                                           \
@@ -37,40 +32,6 @@ __device__ __forceinline__ float dpp_sum16(float v) {
                OP " %6, %6, %6 " PAT "\n\t" OP " %7, %7, %7 " PAT                                        \
                : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]),     \
                  "+v"(v[7]))
-#define S1_DPP16(OP, PAT)                                                                              \
-  asm volatile("s_nop 1\n\t"                                                                           \
-               OP " %0, %0, %0 " PAT "\n\t" OP " %1, %1, %1 " PAT "\n\t" OP " %2, %2, %2 " PAT "\n\t"  \
-               OP " %3, %3, %3 " PAT "\n\t" OP " %4, %4, %4 " PAT "\n\t" OP " %5, %5, %5 " PAT "\n\t"  \
-               OP " %6, %6, %6 " PAT "\n\t" OP " %7, %7, %7 " PAT "\n\t" OP " %8, %8, %8 " PAT "\n\t"  \
-               OP " %9, %9, %9 " PAT "\n\t" OP " %10, %10, %10 " PAT "\n\t" OP " %11, %11, %11 " PAT   \
-               "\n\t" OP " %12, %12, %12 " PAT "\n\t" OP " %13, %13, %13 " PAT "\n\t" OP " %14, %14, %14 " \
-               PAT "\n\t" OP " %15, %15, %15 " PAT                                                      \
-               : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]),     \
-                 "+v"(v[7]), "+v"(v[8]), "+v"(v[9]), "+v"(v[10]), "+v"(v[11]), "+v"(v[12]), "+v"(v[13]), \
-                 "+v"(v[14]), "+v"(v[15]))
-#define S1_DPP_ALL(M)                                                      \
-  if constexpr (MAX) {                                                     \
-    M("v_max_f32_dpp", "quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf");  \
-    M("v_max_f32_dpp", "quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf");  \
-    M("v_max_f32_dpp", "row_half_mirror row_mask:0xf bank_mask:0xf");      \
-    M("v_max_f32_dpp", "row_mirror row_mask:0xf bank_mask:0xf");           \
-  } else {                                                                 \
-    M("v_add_f32_dpp", "quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf");  \
-    M("v_add_f32_dpp", "quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf");  \
-    M("v_add_f32_dpp", "row_half_mirror row_mask:0xf bank_mask:0xf");      \
-    M("v_add_f32_dpp", "row_mirror row_mask:0xf bank_mask:0xf");           \
-  }
-template <bool MAX, int N>
-__device__ __forceinline__ void dpp_reduce16xn(float (&v)[N]) {
-  static_assert(N == 8 || N == 16, "8 or 16 values");
-  if constexpr (N == 16) {
-    S1_DPP_ALL(S1_DPP16)
-  } else {
-    S1_DPP_ALL(S1_DPP8)
-  }
-}
-#undef S1_DPP_ALL
-#undef S1_DPP16
 // Reduce-scatter over the 16 lanes of a row: every lane's v[i] combined,
 // lane li ending with index li's result.  Four butterfly steps, each
 // keeping half of the values: lanes li and li ^ 8 (a rotation by 8), then
