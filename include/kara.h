@@ -196,7 +196,14 @@ kara_status_t kara_validate(const kara_params_t* p, int32_t n_trig, const int32_
 /*
  * Window scoring, Eq. (4), for n_layers layers: writes scores (fp32) and
  * status.  The key states are read from k_pools through the block table.
- * Reductions run in a fixed order, so results are bit-reproducible.
+ * Reductions run in a fixed order, so the same call gives the same bits.  The
+ * order follows from the parameters and from the number of units (triggered
+ * sequences x layers x KV heads): launches of few units split a unit's query
+ * rows over more workgroups.  A sequence's scores may therefore differ in their
+ * last bits, within the step's tolerance, between calls that hold other
+ * sequences or layers beside it (one layer at a time against all at once, say),
+ * and so may its kept set where two scores lie that close.  The fused calls
+ * score in the same way (windows count as units too).
  */
 kara_status_t kara_score_window(const kara_params_t* p, int32_t n_trig, const int32_t* trig,
                                 int32_t n_layers, const void* q, const void* const* k_pools,

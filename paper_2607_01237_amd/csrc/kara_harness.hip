@@ -455,7 +455,8 @@ __global__ __launch_bounds__(kDecThreads, 2) void decode_split_kernel(
 }
 
 // One wave per (layer, sequence, query head) of a sequence longer than one
-// split: its splits' records combined, eight in flight at a time.
+// split: its splits' factors are formed 64 at a time, its records added one by
+// one (the shuffles keep the compiler from unrolling that loop).
 template <int D>
 __global__ __launch_bounds__(256) void decode_combine_kernel(Geom g, int n, const int32_t* __restrict__ seqs,
                                                              const int32_t* __restrict__ seq_lens, int max_len,
@@ -489,7 +490,6 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(Geom g, int n, cons
     const float f = sp < ns ? __builtin_amdgcn_exp2f(w[sp * rec] - M) : 0.f;
     const float lf = sp < ns ? w[sp * rec + 1] * f : 0.f;
     const int cnt = min(64, ns - sp0);
-#pragma unroll 8
     for (int i = 0; i < cnt; ++i) {
       L += __shfl(lf, i, 64);
       const float fi = __shfl(f, i, 64);

@@ -33,7 +33,9 @@ struct RecomputeWs {
 
 // Scratch handed to rocBLAS for the products (rocblas_set_workspace), so it
 // allocates none of its own; a product that needs more fails, which ends the
-// call.  (No size query: between rocblas_start_ and
+// call.  (Measured on ten shapes, 1 x 4096 x 4096 to 8192 x 4096 x 4096 among
+// them: a need of 0, the same results from 256 bytes as from 32 MiB.  No size
+// query: between rocblas_start_ and
 // _stop_device_memory_size_query rocblas_gemm_ex runs the product all the
 // same.  The query of the four shapes cost 1.9 of 6.7 ms per call at 8192 rows
 // of a 4096/12288-wide layer, and added into hidden_out.)

@@ -29,7 +29,7 @@
 // a second kernel adds them in split order.  (Handing the sum to the last
 // split to finish would need a device-scope release/acquire, which on this
 // multi-XCD part writes back and invalidates the whole L2 of the XCD every
-// time.)  No floating-point atomics, so the scores are bit-reproducible.
+// time.)  No floating-point atomics, so the same call gives the same bits.
 #include <algorithm>
 #include <type_traits>
 
@@ -1051,7 +1051,6 @@ void score1_kernel(ScoreArgs a) {
     wait_vm<0>();
     lds_barrier();
     // squared norms, four keys per wave and step (keys past N: below any)
-#pragma unroll 8
     for (int j0 = wave * 4; j0 < kKeys; j0 += NW * 4) {
       const int j = j0 + gq;
       const uint4 v = *(const uint4*)(kpool + key_off[j] + li * 16);
@@ -1333,8 +1332,8 @@ int single_sweep_rows(const Geom& g, int nt, int64_t n_units) {
 template <int NT>
 void launch_s1(const ScoreArgs& a, hipStream_t stream) {
   const dim3 grid((unsigned)a.n_blocks), block(kS1Threads);
-  // (whole instances for the power-of-two window lengths: they save the
-  // few instructions that watch for the last key)
+  // (whole instances for 1024, 1536 and 2048 keys: they save the few
+  // instructions that watch for the last key)
   if constexpr (NT % 8 == 0) {
     if (a.g.N == kS1Waves * 16 * NT) {
       hipLaunchKernelGGL((score1_kernel<NT, true>), grid, block, 0, stream, a);
