@@ -17,6 +17,9 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kNegInf = -__builtin_huge_valf();
+// Lower end of a running maximum: finite, so that a logit of -inf weighs 0 and
+// not 2^(-inf + inf) where a wave has met no other yet; below any finite logit.
+constexpr float kMaxFloor = -3.402823466e38f;
 constexpr int kSplitKeys = KARA_HARNESS_SPLIT_KEYS;
 constexpr int kDecWgTarget = 4096;   // workgroups a launch keeps when its splits grow (16 per CU)
 
@@ -302,7 +305,7 @@ __global__ __launch_bounds__(kDecThreads, 2) void decode_split_kernel(
     }
   };
 
-  float m = kNegInf, lsum = 0.f;   // query li's reference, and this lane's part of its sum
+  float m = kMaxFloor, lsum = 0.f;   // query li's reference, and this lane's part of its sum
   float o[GP][E];                  // query i, this lane's columns, over its row's keys
 #pragma unroll
   for (int i = 0; i < GP; ++i)
@@ -354,7 +357,7 @@ __global__ __launch_bounds__(kDecThreads, 2) void decode_split_kernel(
     mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * c;
     if (__ballot(mx > m + 8.f) != 0ull) {
       const float mn = fmaxf(m, mx);
-      const float f = m == kNegInf ? 0.f : __builtin_amdgcn_exp2f(m - mn);
+      const float f = __builtin_amdgcn_exp2f(m - mn);
       m = mn;
       lsum *= f;
       static_for<0, GP>([&](auto i) __attribute__((always_inline)) {

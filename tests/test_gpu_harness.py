@@ -240,6 +240,57 @@ def test_kv_append(dtype, d):
     print("[case] ok", flush=True)
 
 
+@pytest.mark.parametrize("dtype,Hq,Hkv,d", [("bf16", 8, 2, 128), ("bf16", 4, 2, 64), ("f32", 4, 2, 64), ("f32", 32, 2, 128)])
+def test_decode_of_infinite_logits(dtype, Hq, Hkv, d):
+    # keys whose logits are -inf weigh nothing, also where a wave's first block
+    # or a whole split holds no others; all keys -inf, a +inf or a NaN give NaN
+    # as the softmax does, in their own sequence and KV head alone.  Tolerance
+    # as above (finite logits are of the same size).
+    from paper_2607_01237_amd import kara
+    _need_gpu()
+    dev = torch.device("cuda:0")
+    rng = np.random.default_rng(d)
+    bs, inf = 16, float("inf")
+    # (length, [(first, last, value of the keys' element 0, in KV head 1 alone)])
+    cases = [(40, [(16, 32, -inf, False)]), (40, [(0, 16, -inf, False)]), (64, [(16, 64, -inf, True)]),
+             (300, [(0, 256, -inf, False)]), (1100, [(0, 1099, -inf, False)]), (700, [(32, 96, -inf, True), (256, 512, -inf, False)]),
+             (90, [(0, 90, -inf, True)]), (600, [(0, 600, -inf, False)]), (500, [(300, 301, inf, True)]),
+             (333, [(7, 8, float("nan"), True)]), (200, [])]
+    lens = np.array([c[0] for c in cases], dtype=np.int32)
+    p, table, _ = _geom(rng, len(lens), Hq, Hkv, d, dtype, bs, lens, max_blocks=80)
+    print(f"\n[case] decode of infinite logits {dtype} {Hq}/{Hkv} d={d}", flush=True)
+    params = kara.make_params(p, len(lens))
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator(device="cpu").manual_seed(6)
+    kp, vp = (torch.randn((p["num_pages"], Hkv, bs, d), generator=g).to(dt) for _ in range(2))
+    n = len(lens)
+    q = torch.randn((1, n, Hq, d), generator=g).to(dt)
+    q[..., 0] = q[..., 0].abs() + 0.5
+    for s, (_, spans) in enumerate(cases):
+        for lo, hi, value, one_head in spans:
+            for pos in range(lo, hi):
+                kp[table[s, pos // bs], (1 if one_head else slice(None)), pos % bs, 0] = value
+    T = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(dev)  # noqa: E731
+    max_len = 1200
+    out = torch.full((1, n, Hq, d), -3.0, dtype=torch.float32, device=dev)
+    ws = torch.empty(kara.decode_workspace_size(params, n, 1, max_len), dtype=torch.uint8, device=dev)
+    kara.decode_attention(params, T(np.arange(n, dtype=np.int32)), q.to(dev), [kp.to(dev)], [vp.to(dev)], T(table), T(lens),
+                          max_len, out, ws)
+    torch.cuda.synchronize()
+    got = out.cpu().double()[0]
+    G = Hq // Hkv
+    for s in range(n):
+        pos = np.arange(lens[s])
+        K, V = (t[table[s, pos // bs], :, pos % bs].double() for t in (kp, vp))     # [len][Hkv][d]
+        for h in range(Hkv):
+            x = (q[0, s, h * G:(h + 1) * G].double() @ K[:, h].T) / d ** 0.5
+            want = torch.softmax(x, -1) @ V[:, h]
+            one = got[s, h * G:(h + 1) * G]
+            assert torch.equal(one.isnan(), want.isnan()), (s, h)
+            ok = ~want.isnan()
+            assert ((one - want).abs()[ok] <= 1e-4 + 1e-4 * want.abs()[ok]).all(), (s, h)
+
+
 @pytest.mark.parametrize("n_new", [1, 16, 32, 33])
 @pytest.mark.parametrize("dtype,Hkv,d,bs", [("bf16", 8, 128, 16), ("f32", 3, 64, 7)])
 def test_kv_append_lengths(n_new, dtype, Hkv, d, bs):
