@@ -134,11 +134,13 @@ def test_maximum_compressible_window(window, buffer):
 
 
 
-@pytest.mark.parametrize("window", [600, 1000, 1300, 1536, 2048])
+@pytest.mark.parametrize("window", [600, 1000, 1024, 1100, 1300, 1536, 1700, 1792, 2016, 2048])
 def test_single_sweep_instances(window):
     # bf16, d = 128: every instance of the single-sweep scoring kernel, by
-    # key tiles per wave (16, 24, 32) and whole or ragged tiles: N = 600 and
-    # 1000 (16, ragged), 1300 (24, ragged), 1536 (24, whole), 2048 (32, whole)
+    # key tiles per wave and whether it watches for the last key: N = 600 (12),
+    # 1000 (16), 1024 (16, whole), 1100 (20), 1300 (24), 1536 (24, whole), 1700
+    # (28, ragged) and 1792 (28, all tiles full in the instance that watches),
+    # 2016 (32), 2048 (32, whole)
     cfg = ki.workload("batch8", n_seqs=2, n_layers=1, n_q_heads=4, n_kv_heads=1, window=window,
                       budget=window // 5, prefix=(0, 100), tail=(0, 9), num_pages=600, key_mode="normal")
     _run(cfg)
@@ -283,3 +285,55 @@ def test_resident_keys_far_above_their_reference(dtype, d, window, part):
             print(f"[case] key at {high}, beside {beside}: {rep}", flush=True)
             # (2 x window rows, all but a few of their weight on the placed keys)
             assert ora[0, 0, 0, late] > 0.1 * 2 * window
+
+
+@pytest.mark.parametrize("dtype,d,window", [
+    ("bf16", 64, 200), ("bf16", 64, 449), ("bf16", 64, 1152), ("bf16", 128, 512), ("f32", 64, 500), ("f32", 128, 256),   # resident
+    ("bf16", 128, 600), ("bf16", 128, 1100), ("bf16", 128, 1700), ("bf16", 128, 2048),                                  # single sweep
+    ("bf16", 64, 1200), ("f32", 64, 600),                                                                                # two sweeps
+])
+def test_scores_of_infinite_and_nan_keys(dtype, d, window):
+    # keys whose logits are -inf weigh nothing, also where they fill the tiles
+    # a reference is taken from or all keys but one; a +inf or a NaN key, or no
+    # finite one, makes its own (sequence, KV head) NaN as the softmax does, and
+    # no other
+    import kara_check as kc
+    from paper_2607_01237_amd import kara
+    _need_gpu()
+    inf = float("inf")
+    print(f"\n[case] infinite and NaN keys, {dtype} d={d} N={window}", flush=True)
+    # per sequence and KV head: (positions, value of the keys' element 0)
+    plan = [(slice(3, 4), -inf), (slice(0, 16), -inf), (slice(0, window, 2), -inf), (slice(0, window - 1), -inf),
+            (slice(0, window), -inf), (slice(window // 2, window // 2 + 1), inf), (slice(window - 2, window - 1), float("nan")),
+            (slice(16, 20), -inf)]
+    c = kc.setup(ki.workload("batch8", n_seqs=4, n_layers=1, n_q_heads=4, n_kv_heads=2, dtype=dtype, head_dim=d,
+                             window=window, budget=window // 5, chunk_budget=4, max_chunk_len=4, prefix=(5, 90), tail=(3, 9),
+                             num_pages=-(-(window + 110) // 16) * 4 + 4, key_mode="normal"))
+    bs = c.p["block_size"]
+    c.q[..., 0] = c.q[..., 0].abs() + 0.5
+    keys = torch.empty((4, 2, window, d), dtype=torch.float64)
+    for s in range(4):
+        pos = int(c.geom.win_start[s]) + np.arange(window)
+        pg = torch.as_tensor(c.geom.block_table[s, pos // bs].astype(np.int64), device="cuda")
+        sl = torch.as_tensor((pos % bs).astype(np.int64), device="cuda")
+        for h in range(2):
+            rows, value = plan[2 * s + h]
+            c.kp[0][pg[rows], h, sl[rows], 0] = value
+            keys[s, h] = c.kp[0][pg, h, sl].cpu().double()
+    assert list(c.geom.trig) == [0, 1, 2, 3]
+    ws = torch.empty(kara.workspace_size(c.params, 4, 1), dtype=torch.uint8, device="cuda")
+    scores = torch.full((1, 4, 2, window), -1.0, device="cuda")
+    st = torch.full((4,), -1, dtype=torch.int32, device="cuda")
+    kara.score_window(c.params, c.trig, c.q, c.kp, c.bt, c.seq_lens, c.win_start, scores, st, ws)
+    torch.cuda.synchronize()
+    assert (st == 0).all()
+    got = scores.cpu().numpy()[0]
+    for s in range(4):
+        for h in range(2):
+            x = c.q[0, s, :, 2 * h:2 * h + 2].cpu().double().reshape(-1, d) @ keys[s, h].T / d ** 0.5
+            want = torch.softmax(x, -1).sum(0).numpy()
+            if 2 * s + h in (4, 5, 6):
+                assert np.isnan(want).all() and np.isnan(got[s, h]).all(), (s, h)
+                continue
+            assert np.isfinite(got[s, h]).all(), (s, h)
+            assert (np.abs(got[s, h] - want) <= kc.tol(want)).all(), (s, h, float(np.abs(got[s, h] - want).max()))
