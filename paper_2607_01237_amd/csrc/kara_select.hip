@@ -43,11 +43,13 @@ __host__ __device__ inline size_t sel_lds_bytes(int N, int k) {
 }
 
 // Order-preserving maps to unsigned keys (larger value -> larger key); -0
-// ranks equal to +0, as in a floating-point comparison.
+// ranks equal to +0, as in a floating-point comparison.  Key 0 is nobody's: a
+// lane with nothing left shows it in the argmax rounds.  (A float of all ones,
+// a NaN, would have it; no sum of two floats times an integer is that double.)
 __device__ inline uint32_t ord32(float f) {
   uint32_t u = __float_as_uint(f);
   if ((u & 0x7fffffffu) == 0) u = 0;
-  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+  return (u & 0x80000000u) ? max(~u, 1u) : (u | 0x80000000u);
 }
 __device__ inline uint64_t ord64(double x) {
   uint64_t u = (uint64_t)__double_as_longlong(x);
@@ -263,11 +265,10 @@ __device__ void argmax_top(const KeyT (&key)[EPT], const bool (&elig)[EPT], bool
       const uint32_t hi = wave_max_u32((uint32_t)(bk >> 32));
       const uint32_t lo = wave_max_u32((uint32_t)(bk >> 32) == hi ? (uint32_t)bk : 0u);
       const uint64_t wk = ((uint64_t)hi << 32) | lo;
-      // (a lane with nothing left is no owner of key 0, which a score of all
-      // ones, a NaN, maps to)
-      const uint64_t owners = __ballot(bk == wk && bp != 0x7fffffff);
+      const uint64_t owners = __ballot(bk == wk);
+      const int src = (int)__builtin_ctzll(owners);
       bk = wk;
-      bp = owners ? __builtin_amdgcn_readlane(bp, (int)__builtin_ctzll(owners)) : 0x7fffffff;
+      bp = __builtin_amdgcn_readlane(bp, src);
     }
     const int slot = r & 1;
     if (lane == 0) {
