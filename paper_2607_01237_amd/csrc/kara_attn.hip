@@ -148,7 +148,7 @@ __global__ __launch_bounds__(kAttnThreads, 1) void attn_kernel(AttnArgs a) {
   // descending context length, so the longest blocks start first and the
   // short ones fill the end.  16 sequences of 4K-16K tokens, 32/8 heads:
   // 3.18 ms a layer with a run of whole sequences per XCD (the XCD with the
-  // longest pair finished last), 2.43 to 2.57 ms dealt this way, by box (1010
+  // longest pair finished last), 2.43 to 2.57 ms dealt this way, by card (1010
   // to 1075 TFLOP/s).
   const int64_t slot_x = blockIdx.x >> 3;
   const int64_t piece = slot_x / a.rb_part * 8 + (blockIdx.x & 7);
