@@ -118,7 +118,6 @@ hipError_t launch_swiglu(void* gate, const void* up, int64_t n, hipStream_t stre
 
 // Workspace bytes a call with exactly these arguments uses (n_windows = 1:
 // kara_score_window, kara_compress_window).  Not part of the C ABI: exported for
-// the tests, which hold it against kara_workspace_size and against the limit of
-// the allocation-free entry point.
+// the tests, which hold it against kara_workspace_size.
 extern "C" kara_status_t kara_call_workspace_bytes(const kara_params_t* p, int32_t n_trig, int32_t n_windows,
                                                    int32_t n_layers, size_t* bytes);
